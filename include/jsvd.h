@@ -42,10 +42,9 @@ extern "C" {
 
 #define JSVD_OK 0
 #define JSVD_NOT_CONVERGED 1   /* max_sweeps reached with proper rotations left */
-/* 2 is not used: a Cholesky pivot that is not positive (Section 4.1 is silent
- * on it; the pivot block Gram matrix is then only semidefinite) is not an
- * error here -- it makes its row of R zero, the iteration goes on and
- * jsvd_info.chol_breakdowns counts it; a NaN or infinite pivot returns
+/* 2 is not used: a pivot block Gram matrix that is only semidefinite (Section
+ * 4.1 is silent on it) is not an error here -- the iteration goes on and
+ * jsvd_info.chol_breakdowns counts it; a NaN or infinity in it returns
  * JSVD_NONFINITE. */
 #define JSVD_NONFINITE 3       /* a NaN or infinity appeared in the input or the iteration */
 #define JSVD_HIP_ERROR 4       /* a HIP runtime call failed */
@@ -124,8 +123,10 @@ typedef struct {
     int64_t proper_rotations;  /* of which with cos != 1 (Section 4.3, subphase 4) */
     int64_t inner_sweeps;      /* inner sweeps summed over all pivot block-pairs */
     int64_t pair_updates;      /* pivot block-pairs whose V'_pq was applied */
-    int32_t chol_breakdowns;   /* non-positive Cholesky pivots met (the block Gram matrix was
-                                  only semidefinite); each makes its row of R zero */
+    int32_t chol_breakdowns;   /* diagonal entries of the pivot Gram matrices that were not
+                                  positive after an inner iteration, or Cholesky pivots that
+                                  were not (opts.scaled, block_w 64): the block Gram matrix
+                                  was only semidefinite */
     int32_t hyp_clamps;        /* |coth 2phi| <= 1 replaced by 5/4 (Section 4.3.1) */
     int32_t block_w;           /* w actually used */
     int32_t n_blocks;          /* block-columns in the pivot strategy (with padding) */

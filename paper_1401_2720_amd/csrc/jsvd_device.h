@@ -231,11 +231,61 @@ __device__ __forceinline__ void rotation_fast(double hpp, double hqq, double hpq
     cs = (act >= kSqrt2OverEps) ? 1.0 : c;
 }
 
+// tan and cos of the rotation that zeroes h_pq, eqs. (4.3)-(4.6), by a chain
+// of dependent operations less than half as long as rotation_fast's.  With
+// d = h_qq - t h_pp and b = 2 h_pq (ct 2phi = t d / b) the smaller root of
+// (4.4) is |b| / (|d| + sqrt(d^2 + t b^2)), and cos = 1 / sqrt(1 + t tan^2).
+// What V' needs is that cos belongs to the double tan: cos is computed from
+// tan, with the rounding error of 1 + t tan^2 carried along, so that
+// cos^2 (1 + t tan^2) - 1 stays within 1.5 eps and averages zero (rotation:
+// within 5 eps); tan itself is within 4 eps of the exact root, as
+// rotation's (averages 0.65 and 0.73 eps over random pairs).  Each
+// reciprocal and root is the hardware seed (relative error below 2^-22) and
+// one step of third order.  Valid where in_trig_range(h_pp, h_qq) holds and
+// the pair rotates, else the results are not used.
+__device__ __forceinline__ void rotation_h(double hpp, double hqq, double hpq, bool hyp,
+                                           double &tn, double &cs, bool &clamped) {
+    const double b = 2.0 * hpq, d = hyp ? hqq + hpp : hqq - hpp;
+    const double ad = fabs(d), ab = fabs(b);
+    clamped = hyp && ad <= ab;
+    const double x = hyp ? (ad - ab) * (ad + ab) : fma(d, d, b * b);
+    double y = __builtin_amdgcn_rsq(x);
+    const double s = x * y;
+    double e = fma(-s, y, 1.0);
+    const double den = ad + fma(s * e, fma(e, 0.375, 0.5), s);
+    double z = __builtin_amdgcn_rcp(den);
+    e = fma(-den, z, 1.0);
+    z = fma(z, fma(e, e, e), z);
+    double q = ab * z;
+    q = fma(fma(-den, q, ab), z, q);
+    q = clamped ? 0.5 : q;  // ct 2phi = 5/4
+    // the sign of t d / b (of -1 / b for d = 0: the larger entry stays h_pp)
+    const bool neg = (hyp ? d >= 0.0 : !(d > 0.0)) != __builtin_signbit(b);
+    tn = neg ? -q : q;
+    const double mt = hyp ? -tn : tn;
+    const double u = fma(mt, tn, 1.0);
+    double ul = fma(mt, tn, 1.0 - u);  // 1 + t tan^2 = u + ul (1 - u exact for u >= 1/2)
+    if (hyp) ul = u >= 0.5 ? ul : 0.0;
+    y = __builtin_amdgcn_rsq(u);
+    const double h = u * y, hl = fma(ul, y, fma(u, y, -h));
+    e = fma(-hl, y, fma(-h, y, 1.0));
+    cs = fma(y * e, fma(e, 0.375, 0.5), y);
+}
+
 // h_pp and h_qq in [2^-450, 2^450]: then the relative orthogonality test
 // can be taken on squares, and a rotating pair has |h_pq| in [2^-500, 2^450],
 // inside the range of rotation_fast.
 __device__ __forceinline__ bool in_trig_range(double hpp, double hqq) {
     return fmin(hpp, hqq) >= 0x1p-450 && fmax(hpp, hqq) <= 0x1p450;
+}
+
+// The same from the upper halves of the representations (a negative value
+// compares above the range; the range's top is 2^450 exclusive).
+__device__ __forceinline__ bool in_trig_range_bits(double hpp, double hqq) {
+    constexpr unsigned lo = (1023u - 450u) << 20, span = 900u << 20;
+    const unsigned p = (unsigned)(__builtin_bit_cast(unsigned long long, hpp) >> 32) - lo;
+    const unsigned q = (unsigned)(__builtin_bit_cast(unsigned long long, hqq) >> 32) - lo;
+    return max(p, q) < span;
 }
 
 __device__ __forceinline__ bool in_fast_range(double v) {

@@ -204,6 +204,7 @@ int get_inner_table(jsvd_handle_s *h, int bw, int kind, const unsigned char **ou
                 flat.push_back(static_cast<unsigned char>(pr.first));
                 flat.push_back(static_cast<unsigned char>(pr.second));
             }
+        if (bw <= 64) position_tables(t, flat);  // jacobi_kernel's
         DeviceTable d;
         d.bytes = flat.size();
         HIP_TRY(hipMalloc(&d.ptr, d.bytes));

@@ -22,6 +22,18 @@ bool make_table(int order, int kind, Table &out);
 // the pairs of each step reordered for conflict-free LDS access in the inner
 // kernels (a permutation within each step; the steps and pairs unchanged)
 void order_for_banks(Table &t);
+// Appends to out the tables of the inner kernel on the Gram matrix, which
+// keeps the pair in slot k of a step at positions k (its first column x) and
+// np + k (its second, y), np = pairs per step.  Per step and slot 8 bytes: the
+// positions of x and y in the step before and in the next one (the steps
+// taken cyclically), x, y, flags, and a slot; then the position of every
+// column in step 0.  From one step to the next a slot keeps one column and
+// sends the other to the slot in the last byte.  Flags: 1 if x > y; 2 if the
+// column kept from the step before is y (in step 0 either may count as
+// kept); 4 if that same column is kept again (set in the last step).  The
+// first columns of a step all go to different slots of the next one, and the
+// second ones too.
+void position_tables(const Table &t, std::vector<unsigned char> &out);
 // The step-to-step groups of a strategy table whose consecutive steps
 // exchange partners inside groups of two pairs, (a0 a1), (b0 b1) -> pairs of
 // {a0, a1} x {b0, b1}: per step s < order - 2 and group, 8 ints {ia, ib, jx,

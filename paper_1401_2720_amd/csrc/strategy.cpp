@@ -312,6 +312,71 @@ void order_for_banks(Table &t) {
     }
 }
 
+void position_tables(const Table &t, std::vector<unsigned char> &out) {
+    const int ns = (int)t.size(), np = (int)t[0].size(), nc = 2 * np;
+    std::vector<std::vector<int>> mate(ns, std::vector<int>(nc));
+    for (int s = 0; s < ns; ++s)
+        for (const Pair &pr : t[s]) {
+            mate[s][pr.first] = pr.second;
+            mate[s][pr.second] = pr.first;
+        }
+    // Slots.  A pair of step s + 1 takes its two columns from two slots of
+    // step s, and a slot's two columns go to two pairs: with the slots as
+    // vertices and the new pairs as edges that is a set of cycles.  Along each
+    // cycle a slot keeps one column, whose new pair it takes, and sends the
+    // other to the slot before it.
+    std::vector<std::vector<int>> slot(ns, std::vector<int>(nc)), kept(ns, std::vector<int>(np)),
+        sent(ns, std::vector<int>(np));
+    for (int k = 0; k < np; ++k) {
+        slot[0][t[0][k].first] = slot[0][t[0][k].second] = k;
+        kept[0][k] = t[0][k].first;
+    }
+    for (int s = 0; s + 1 < ns; ++s) {
+        std::vector<std::pair<int, int>> held(np, {-1, -1});
+        for (int c = 0; c < nc; ++c) {
+            auto &h = held[slot[s][c]];
+            (h.first < 0 ? h.first : h.second) = c;
+        }
+        std::vector<char> done(np, 0);
+        for (int k0 = 0; k0 < np; ++k0)
+            for (int k = k0, c = held[k0].first; !done[k];) {
+                done[k] = 1;
+                const int in = mate[s + 1][c];
+                kept[s + 1][k] = c;
+                sent[s][k] = held[k].first == c ? held[k].second : held[k].first;
+                slot[s + 1][c] = slot[s + 1][in] = k;
+                k = slot[s][in];
+                c = held[k].first == in ? held[k].second : held[k].first;
+            }
+    }
+    // Places.  The pairs of a step and of the next one, as edges between
+    // columns, form even cycles; first and second alternate along them.
+    std::vector<std::vector<int>> pos(ns, std::vector<int>(nc, -1));
+    for (int s = 0; s < ns; ++s)
+        for (int c0 = 0; c0 < nc; ++c0)
+            for (int c = c0; pos[s][c] < 0;) {
+                const int d = mate[s][c];
+                pos[s][c] = slot[s][c];
+                pos[s][d] = slot[s][d] + np;
+                c = mate[(s + 1) % ns][d];
+            }
+    for (int s = 0; s < ns; ++s) {
+        const auto &prev = pos[(s + ns - 1) % ns], &next = pos[(s + 1) % ns];
+        std::vector<int> col(nc);
+        for (int c = 0; c < nc; ++c) col[pos[s][c]] = c;
+        for (int k = 0; k < np; ++k) {
+            const int x = col[k], y = col[np + k];
+            const bool last = s + 1 == ns;
+            const int flags = (x > y ? 1 : 0) | (kept[s][k] == y ? 2 : 0) |
+                              (last || sent[s][k] != kept[s][k] ? 4 : 0);
+            for (int v : {prev[x], prev[y], next[x], next[y], x, y, flags,
+                          last ? 0 : slot[s + 1][sent[s][k]]})
+                out.push_back((unsigned char)v);
+        }
+    }
+    for (int c = 0; c < nc; ++c) out.push_back((unsigned char)pos[0][c]);
+}
+
 bool make_quads(const Table &t, std::vector<int> &out) {
     out.clear();
     if (t.size() < 2) return false;
