@@ -5,6 +5,8 @@
 // 16-column sub-blocks on the Cholesky factor of a 128-column pivot block).
 #pragma once
 
+#include <type_traits>
+
 #include "jsvd_device.h"
 
 namespace jsvd {
@@ -51,19 +53,18 @@ __device__ __forceinline__ bool trig_pair(double hpp, double hqq, double hpq, do
 // Problems with many columns take the two-level method of the dense path
 // inside their workgroup: block-columns of kBlkW columns, the closest
 // parallel strategy of order nb on the blocks, and for every pivot
-// block-pair the Gram matrix (2.7), its Cholesky factor R (Section 4.1),
-// one sweep of the pointwise method on R accumulating V' (Section 4.3,
-// block-oriented) and [G_p G_q] V', [V_p V_q] V' (2.9), skipped when the
-// pair did not rotate (Section 4.4).  A pair whose Gram matrix already
-// passes the relative orthogonality test everywhere is left alone.  Up to
-// kBlkPairs pivot pairs are in flight: two waves per pair form the Gram
-// matrix (rows split, FP64 MFMA) and apply V' (FP64 MFMA), one wave per pair
-// factors it, and 8 lanes per pivot pair of R run the inner sweep.  G and V
-// stay in their global buffers; R and V' live in LDS, small enough for two
-// workgroups (two problems) per CU, which hide each other's latencies.
+// block-pair the Gram matrix (2.7), one sweep of the pointwise method on it
+// accumulating V' (Section 4.3, block-oriented) and [G_p G_q] V',
+// [V_p V_q] V' (2.9), skipped when the pair did not rotate (Section 4.4).  A
+// pair whose Gram matrix already passes the relative orthogonality test
+// everywhere is left alone.  Up to kBlkPairs pivot pairs are in flight: two
+// waves per pair form the Gram matrix (rows split, FP64 MFMA) and apply V'
+// (FP64 MFMA).  G and V stay in their global buffers; H and V' live in LDS,
+// small enough for two workgroups (two problems) per CU, which hide each
+// other's latencies.
 constexpr int kBlkW = 16, kBlkBW = 2 * kBlkW, kBlkLD = kBlkBW + 1, kBlkPairs = 4;
 constexpr int kBlkThreads = 512;  // 8 waves: two per pivot pair in the Gram and update phases
-constexpr int kBlkMat = kBlkBW * kBlkLD;  // doubles of one R or V'
+constexpr int kBlkMat = kBlkBW * kBlkLD;  // doubles of one H or V'
 
 // X[0:rows, cols of pq] <- X[0:rows, cols of pq] V' for the rows of one
 // wave (16-row slices from row 16 sub, stride 16 nsub), V' row-major in LDS
@@ -98,41 +99,308 @@ __device__ __forceinline__ void blk_rows_update(double *X, int ldx, int rows, in
     }
 }
 
-// The sweep loop of the blocked method on one problem (G: m x n, ld m; V:
-// n x n, ld n, identity on entry, or null).  lds holds kBlkLdsDoubles.
-// Returns the sweeps performed (max_sweeps <= 0xffff), plus kBlkConverged
-// when a sweep performed no proper rotation and kBlkNonfinite when a
-// Cholesky pivot was NaN or infinite.  stats (LDS, three ints the caller
-// zeroes, or null) accumulates the rotations, the proper rotations and the
-// pivot pairs whose V' was applied.
-constexpr int kBlkLdsDoubles = 2 * kBlkPairs * kBlkMat;  // R, V' (the Gram sums use V' space)
-static_assert(kBlkPairs * 3 * 4 * 64 <= kBlkPairs * kBlkMat, "Gram partial sums fit in V' space");
+// The inner sweep works on the 32 x 32 Gram matrices of the group's pivot
+// pairs as jacobi_kernel does on its one (two-sided rotations, positions,
+// slots; see there), with the roles spread over the workgroup so that the
+// four matrices fill them: wave 0 computes the rotations of all four (16
+// lanes each, a step ahead), waves 1-3 rotate H, waves 4-7 V'.  Both copies
+// of an H share one array: even steps keep entry (x, y) at (min, max), odd
+// ones at (max, min).
+struct BlkLds {
+    double H[kBlkPairs][kBlkMat];                         // then V', row-major
+    __align__(16) double xch[kBlkPairs][2][kBlkW * kBlkBW];  // columns of V' on their way;
+                                                          // before that the Gram sums
+    double diag[kBlkPairs][kBlkBW];
+    double2 prm[2][kBlkPairs][kBlkW];                     // published rotations: tan, +-cos
+    unsigned dst[2][kBlkPairs][kBlkW];                    // next positions (times 8)
+    uint2 tbl[(kBlkBW - 1) * kBlkW];                      // position_tables' entries
+    unsigned vctl[(kBlkBW - 1) * kBlkW];                  // V waves' control words
+};
+constexpr int kBlkLdsDoubles = (int)(sizeof(BlkLds) / sizeof(double));
+static_assert(sizeof(BlkLds) % sizeof(double) == 0, "whole doubles");
+static_assert(3 * 4 * 64 <= 2 * kBlkW * kBlkBW, "Gram partial sums fit in xch");
 static_assert(kBlkLdsDoubles == kBatchBlockLds, "host LDS bound of the blocked method");
-static_assert(kBlkBW == kBatchInnerOrder, "the host orders this table's pairs for the LDS banks");
+static_assert(kBlkBW == kBatchInnerOrder && kBlkPairs == 4 && kBlkThreads == 512, "wave roles");
 
 constexpr int kBlkConverged = 1 << 16, kBlkNonfinite = 1 << 17;
 
+// Wave 0 of blk_inner_sweep: lane 16 mx + k has pair k of matrix mx.
+struct BlkRotations {
+    static constexpr int NP = kBlkW, NS = kBlkBW - 1, LD = kBlkLD;
+    BlkLds &L;
+    const int mx, k, cm;
+    const bool act;
+    double off = 0.0;  // h_pq after the pair's rotation,
+    unsigned off_at = 0;  // and where it goes
+    // the next step's columns, as in jacobi_kernel
+    unsigned h00 = 0, h01 = 0, h10 = 0, h11 = 0, Ia = 0, Jb = 0;
+    bool fa = false, fb = false;
+    int rots = 0, prop = 0;
+
+    __device__ __forceinline__ BlkRotations(BlkLds &lds, int lane, const int *need, const int *cmax)
+        : L(lds), mx(lane / NP), k(lane % NP), cm(cmax[lane / NP]), act(need[lane / NP] != 0) {}
+
+    template <int PAR>
+    static __device__ __forceinline__ unsigned at(unsigned x8, unsigned y8) {
+        return PAR ? max(x8, y8) * LD + min(x8, y8) : min(x8, y8) * LD + max(x8, y8);
+    }
+
+    // decide, compute and publish the pair's rotation in the step of parity
+    // PAR and table entry t; nxt: the next step's entry
+    template <int PAR>
+    __device__ __forceinline__ void rotate(uint2 t, uint2 nxt, double hpp, double hqq, double hpq) {
+        constexpr double tol2 = kEps * kEps * kBlkBW;  // c(eps)^2 = 2w eps^2, exact
+        const int cp = t.y & 0xff, cq = (t.y >> 8) & 0xff;
+        hpp = act ? hpp : 1.0;
+        hqq = act ? hqq : 1.0;
+        hpq = act ? hpq : 0.0;
+        const unsigned flip = (t.y & 0x10000u) << 15;
+        const double up = __builtin_bit_cast(
+            double, __builtin_bit_cast(unsigned long long, hqq - hpp) ^ ((unsigned long long)flip << 32));
+        const bool swap = (up > 0.0) & (max(cp, cq) < cm);
+        const unsigned mine = (unsigned)(__builtin_amdgcn_ballot_w64(swap) >> (NP * mx));
+        const unsigned dp8 = ((t.x >> 16) & 0xff) * 8, dq8 = (t.x >> 24) * 8;
+        const unsigned np8 = swap ? dq8 : dp8, nq8 = swap ? dp8 : dq8;
+        bool rot = !(hpq * hpq <= tol2 * hpp * hqq);
+        double tn, cs;
+        bool clamped;
+        rotation_h(hpp, hqq, hpq, false, tn, cs, clamped);
+        if (!in_trig_range_bits(hpp, hqq)) {  // IEEE operations, as in jacobi_kernel
+            const double tol = kEps * sqrt((double)kBlkBW);
+            rot = hpq != 0.0 && !(fabs(hpq) <= tol * sqrt(hpp) * sqrt(hqq));
+            rotation(hpp, hqq, hpq, 1, tn, cs, clamped);
+        }
+        tn = rot ? tn : 0.0;
+        cs = rot ? cs : 1.0;
+        off = rot ? 0.0 : hpq;
+        rots += rot ? 1 : 0;
+        prop += (rot && cs != 1.0) ? 1 : 0;
+        char *const db = reinterpret_cast<char *>(L.diag[mx]);
+        L.prm[PAR][mx][k] = make_double2(tn, swap ? -cs : cs);
+        L.dst[PAR][mx][k] = np8 | nq8 << 16;
+        *reinterpret_cast<double *>(db + np8) = fma(-tn, hpq, hpp);
+        *reinterpret_cast<double *>(db + nq8) = fma(tn, hpq, hqq);
+        off_at = at<1 - PAR>(dp8, dq8);
+        const unsigned sp = nxt.x & 0xff, sq = (nxt.x >> 8) & 0xff;
+        Ia = sp % NP;
+        Jb = sq % NP;
+        const unsigned r8 = (sp ^ ((mine >> Ia) & 1u) * NP) * 8, c8 = (sq ^ ((mine >> Jb) & 1u) * NP) * 8;
+        const unsigned r8o = r8 ^ (NP * 8), c8o = c8 ^ (NP * 8);
+        fa = r8 >= NP * 8;
+        fb = c8 >= NP * 8;
+        h00 = at<PAR>(r8, c8);
+        h01 = at<PAR>(r8, c8o);
+        h10 = at<PAR>(r8o, c8);
+        h11 = at<PAR>(r8o, c8o);
+        asm volatile("" : "+v"(h00), "+v"(h01), "+v"(h10), "+v"(h11), "+v"(off_at));
+    }
+
+    // step st of parity PAR: the rotation of step st + 1
+    template <int PAR>
+    __device__ __forceinline__ void ahead(int st, uint2 &t0, uint2 &t1) {
+        char *const hb = reinterpret_cast<char *>(L.H[mx]);
+        auto ld = [&](unsigned o) { return *reinterpret_cast<const double *>(hb + o); };
+        const double x00 = ld(h00), x01 = ld(h01), x10 = ld(h10), x11 = ld(h11);
+        const double2 ra = L.prm[PAR][mx][Ia], rb = L.prm[PAR][mx][Jb];
+        const double hpp = L.diag[mx][k], hqq = L.diag[mx][k + NP];
+        *reinterpret_cast<double *>(hb + off_at) = off;
+        const uint2 t = t0;
+        t0 = t1;
+        t1 = L.tbl[min(st + 3, NS - 1) * NP + k];
+        const double ga = fa ? ra.x : -ra.x, gb = fb ? rb.x : -rb.x;
+        const double x0 = fma(gb, x01, x00), x1 = fma(gb, x11, x10);
+        rotate<1 - PAR>(t, t0, hpp, hqq, fabs(ra.y * rb.y) * fma(ga, x1, x0));
+    }
+};
+
+// H waves of blk_inner_sweep: the 2 x 2 block of pairs (I, J), I < J, of one
+// matrix in a step of parity PAR.
+template <int PAR>
+__device__ __forceinline__ void blk_rotate_block(BlkLds &L, int m, int I, int J) {
+    constexpr int NP = kBlkW, LD = kBlkLD;
+    char *const hb = reinterpret_cast<char *>(L.H[m]);
+    auto ld = [&](int x, int y) {  // x < y
+        return *reinterpret_cast<const double *>(hb + 8 * (PAR ? y * LD + x : x * LD + y));
+    };
+    const double b00 = ld(I, J), b01 = ld(I, J + NP), b10 = ld(J, I + NP), b11 = ld(I + NP, J + NP);
+    const double2 ri = L.prm[PAR][m][I], rj = L.prm[PAR][m][J];
+    const unsigned di = L.dst[PAR][m][I], dj = L.dst[PAR][m][J];
+    const double cc = fabs(ri.y * rj.y);
+    const double x0 = fma(-rj.x, b01, b00), y0 = fma(rj.x, b00, b01);
+    const double x1 = fma(-rj.x, b11, b10), y1 = fma(rj.x, b10, b11);
+    const unsigned A0 = di & 0xffff, A1 = di >> 16, B0 = dj & 0xffff, B1 = dj >> 16;
+    auto put = [&](unsigned x8, unsigned y8, double v) {
+        *reinterpret_cast<double *>(hb + BlkRotations::at<1 - PAR>(x8, y8)) = v;
+    };
+    put(A0, B0, cc * fma(-ri.x, x1, x0));
+    put(A1, B0, cc * fma(ri.x, x0, x1));
+    put(A0, B1, cc * fma(-ri.x, y1, y0));
+    put(A1, B1, cc * fma(ri.x, y0, y1));
+}
+
+// V waves of blk_inner_sweep: one slot of matrix m in step st of parity PAR;
+// vk the kept column, vr the other one, ctl the slot's control word.
+template <int PAR>
+__device__ __forceinline__ void blk_rotate_v(BlkLds &L, int m, int sl, int vrow, int st, double2 &vk,
+                                             double2 &vr, unsigned &ctl) {
+    constexpr int NP = kBlkW, NS = kBlkBW - 1, BW = kBlkBW;
+    if (st > 0) vr = *reinterpret_cast<const double2 *>(&L.xch[m][1 - PAR][sl * BW + vrow]);
+    const double2 r = L.prm[PAR][m][sl];
+    const unsigned long long mask = (unsigned long long)(ctl & 0x80000000u) << 32;
+    const double tk = __builtin_bit_cast(double, __builtin_bit_cast(unsigned long long, r.x) ^ mask);
+    const double c = fabs(r.y);
+    const double2 k1 = make_double2(c * fma(-tk, vr.x, vk.x), c * fma(-tk, vr.y, vk.y));
+    const double2 r1 = make_double2(c * fma(tk, vk.x, vr.x), c * fma(tk, vk.y, vr.y));
+    const bool same = ((ctl & 0x40000000u) != 0) != (r.y < 0.0);
+    vk = make_double2(same ? k1.x : r1.x, same ? k1.y : r1.y);
+    vr = make_double2(same ? r1.x : k1.x, same ? r1.y : k1.y);
+    if (st + 1 < NS) {
+        *reinterpret_cast<double2 *>(reinterpret_cast<char *>(&L.xch[m][PAR][vrow]) + (ctl & 0xffff)) = vr;
+        ctl = L.vctl[(st + 1) * NP + sl];
+    }
+}
+
+// One inner sweep on the matrices k with need[k] (H and diag set); V' into
+// H, row-major; their rotations added to rotk, the proper ones of this lane
+// to prop.  cmax[k]: columns of pair k from there on are padding.  All 512
+// threads; each role has its own loop, with the same barriers.
+__device__ __forceinline__ void blk_inner_sweep(BlkLds &L, const int *need, const int *cmax,
+                                                int *rotk, int &prop) {
+    constexpr int NP = kBlkW, NS = kBlkBW - 1, LD = kBlkLD;
+    static_assert(NS % 2 == 1, "the last step is an even one");
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (wave == 0) {
+        __builtin_amdgcn_s_setprio(3);
+        BlkRotations r(L, lane, need, cmax);
+        const int k = r.k;
+        uint2 t0 = L.tbl[NP + k], t1 = L.tbl[2 * NP + k];
+        r.rotate<0>(L.tbl[k], t0, L.diag[r.mx][k], L.diag[r.mx][k + NP],
+                    L.H[r.mx][k * LD + k + NP]);
+        __syncthreads();
+        for (int st = 0; st + 1 < NS; st += 2) {
+            r.ahead<0>(st, t0, t1);
+            __syncthreads();
+            r.ahead<1>(st + 1, t0, t1);
+            __syncthreads();
+        }
+        __syncthreads();
+        if (r.rots) atomicAdd(&rotk[r.mx], r.rots);
+        prop += r.prop;
+        __builtin_amdgcn_s_setprio(0);
+    } else if (wave < 4) {
+        // both halves of matrix wave - 1 (64 blocks each), and of waves 1 and
+        // 2 half of matrix 3
+        int bI[2], bJ[2];
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const int ht = lane + 64 * u, g = ht / NP, l = ht % NP;
+            const bool first = l < NP - 1 - g;
+            bI[u] = first ? g : NP - 2 - g;
+            bJ[u] = first ? g + 1 + l : l;
+        }
+        const int m = wave - 1;
+        const int I3 = wave == 2 ? bI[1] : bI[0], J3 = wave == 2 ? bJ[1] : bJ[0];
+        auto step = [&](auto par) __attribute__((always_inline)) {
+            constexpr int PAR = decltype(par)::value;
+            blk_rotate_block<PAR>(L, m, bI[0], bJ[0]);
+            blk_rotate_block<PAR>(L, m, bI[1], bJ[1]);
+            if (wave < 3) blk_rotate_block<PAR>(L, 3, I3, J3);
+            __syncthreads();
+        };
+        __syncthreads();
+        for (int st = 0; st + 1 < NS; st += 2) {
+            step(std::integral_constant<int, 0>{});
+            step(std::integral_constant<int, 1>{});
+        }
+        __syncthreads();
+    } else {
+        // matrix vm, slots 4 u + lane / 16, two rows per lane
+        const int vm = wave == 4 ? 3 : wave - 5, vrow = 2 * (lane % NP), vq = lane / NP;
+        double2 vk[4], vr[4];
+        unsigned ctl[4];
+        auto kept_col = [&](int e, int &ck, int &cr) __attribute__((always_inline)) {
+            const unsigned t = L.tbl[e].y;
+            const bool ky = (t & 0x20000u) != 0;
+            ck = (ky ? t >> 8 : t) & 0xff;
+            cr = (ky ? t : t >> 8) & 0xff;
+        };
+        auto step = [&](auto par, int st) __attribute__((always_inline)) {
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                blk_rotate_v<decltype(par)::value>(L, vm, 4 * u + vq, vrow, st, vk[u], vr[u], ctl[u]);
+            __syncthreads();
+        };
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {  // V' = I
+            const int sl = 4 * u + vq;
+            int ck, cr;
+            kept_col(sl, ck, cr);
+            vk[u] = make_double2(vrow == ck ? 1.0 : 0.0, vrow + 1 == ck ? 1.0 : 0.0);
+            vr[u] = make_double2(vrow == cr ? 1.0 : 0.0, vrow + 1 == cr ? 1.0 : 0.0);
+            ctl[u] = L.vctl[sl];
+        }
+        __syncthreads();
+        for (int st = 0; st + 1 < NS; st += 2) {
+            step(std::integral_constant<int, 0>{}, st);
+            step(std::integral_constant<int, 1>{}, st + 1);
+        }
+        step(std::integral_constant<int, 0>{}, NS - 1);
+        double *const v = L.H[vm];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            int ck, cr;
+            kept_col((NS - 1) * NP + 4 * u + vq, ck, cr);
+            v[vrow * LD + ck] = vk[u].x;
+            v[(vrow + 1) * LD + ck] = vk[u].y;
+            v[vrow * LD + cr] = vr[u].x;
+            v[(vrow + 1) * LD + cr] = vr[u].y;
+        }
+    }
+    __syncthreads();
+}
+
+// The sweep loop of the blocked method on one problem (G: m x n, ld m; V:
+// n x n, ld n, identity on entry, or null).  lds holds kBlkLdsDoubles; jac:
+// position_tables' tables of order 32.
+// Returns the sweeps performed (max_sweeps <= 0xffff), plus kBlkConverged
+// when a sweep performed no proper rotation and kBlkNonfinite when a pivot
+// Gram matrix held a NaN or an infinity.  stats (LDS, three ints the caller
+// zeroes, or null) accumulates the rotations, the proper rotations and the
+// pivot pairs whose V' was applied.
 __device__ __forceinline__ int blocked_sweeps(double *G, double *V, int m, int n, int max_sweeps,
                                               const int *tbl_order, const int64_t *tbl_off,
-                                              const unsigned char *tbls, double *lds,
-                                              int *stats = nullptr) {
+                                              const unsigned char *tbls, const unsigned char *jac,
+                                              double *lds, int *stats = nullptr) {
     __shared__ int2 s_pq[kBlkPairs];
-    __shared__ int s_need[kBlkPairs], s_rotk[kBlkPairs], s_prop, s_bad;
+    __shared__ int s_need[kBlkPairs], s_rotk[kBlkPairs], s_cmax[kBlkPairs], s_prop, s_bad;
+    __shared__ unsigned char s_pos0[kBlkBW];
+    BlkLds &L = *reinterpret_cast<BlkLds *>(lds);
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int i16 = lane & 15, grp = lane >> 4;
     const int nb = (n + kBlkW - 1) / kBlkW;
     const int NB = tbl_order[nb];
     const unsigned char *btbl = tbls + tbl_off[NB >> 1];
-    const unsigned char *itbl = tbls + tbl_off[kBlkBW >> 1];
     const double tol = kEps * sqrt((double)kBlkBW);  // c(eps) at the inner level, n^ = 2w
-    double *Rm = lds, *Vm = lds + kBlkPairs * kBlkMat, *red = Vm;  // red: before V' is set
+    const double tol2 = kEps * kEps * kBlkBW;
     const int wk = wave >> 1, sub = wave & 1;  // pair and half of a wave's Gram / update work
+
+    constexpr int kEntries = (kBlkBW - 1) * kBlkW;
+    static_assert(kEntries <= kBlkThreads, "one table entry per thread");
+    if (tid < kEntries) {
+        const uint2 t = reinterpret_cast<const uint2 *>(jac)[tid];
+        L.tbl[tid] = t;
+        // where the sent column goes (bytes in xch); bit 31: the kept column is
+        // y; bit 30: it is kept again
+        L.vctl[tid] = (t.y >> 24) * (kBlkBW * 8) | (t.y & 0x20000u) << 14 | (t.y & 0x40000u) << 12;
+    }
+    if (tid < kBlkBW) s_pos0[tid] = jac[8 * kEntries + tid];
 
     int sweeps = 0, result = 0;
     if (tid == 0) s_bad = 0;
     while (sweeps < max_sweeps) {
         if (tid == 0) s_prop = 0;
-        int prop = 0;  // proper rotations of this lane's pivot pairs (lanes x == 0)
+        int prop = 0;  // proper rotations of this lane's pivot pairs (wave 0)
         for (int st = 0; st < NB - 1; ++st) {
             const unsigned char *row = btbl + (size_t)st * NB;
             int slot = 0;
@@ -185,50 +453,71 @@ __device__ __forceinline__ int blocked_sweeps(double *G, double *V, int m, int n
                         }
                     }
                 }
-                for (int wv = 0; wv < 2; ++wv) {
-                    if (wk < npg && sub == wv) {
-                        double *Rk = Rm + wk * kBlkMat;
+                double *const red = &L.xch[wk][0][0];
+                if (wk < npg && sub == 0) {
+#pragma unroll
+                    for (int t = 0; t < 3; ++t)
+#pragma unroll
+                        for (int v = 0; v < 4; ++v) red[(t * 4 + v) * 64 + lane] = acc[t][v];
+                }
+                __syncthreads();
+                // entry (i, j), i <= j, of H to its place; padding columns become
+                // unit vectors
+                if (wk < npg && sub == 1) {
+#pragma unroll
+                    for (int t = 0; t < 3; ++t)
+#pragma unroll
+                        for (int v = 0; v < 4; ++v) {
+                            const int i = (t == 2 ? 16 : 0) + grp + 4 * v, j = (t == 0 ? 0 : 16) + i16;
+                            const bool ok = pair_col(i, kBlkW, pq) < n && pair_col(j, kBlkW, pq) < n;
+                            const double h = red[(t * 4 + v) * 64 + lane] + acc[t][v];
+                            acc[t][v] = ok ? h : (i == j ? 1.0 : 0.0);
+                            const int pi = s_pos0[i], pj = s_pos0[j];
+                            if (i < j) L.H[wk][min(pi, pj) * kBlkLD + max(pi, pj)] = acc[t][v];
+                            if (i == j) L.diag[wk][pi] = acc[t][v];
+                        }
+                    if (lane == 0) {
+                        const int nq = n - pq.y * kBlkW;
+                        s_cmax[wk] = nq > 0 ? kBlkW + min(kBlkW, nq) : min(kBlkW, n - pq.x * kBlkW);
+                    }
+                }
+                __syncthreads();
+
+                // (2) which pairs need the inner sweep: some (i, j) fails the
+                // relative orthogonality test on H (reading: <= passes), on
+                // squares where they cannot leave the normal range
+                if (wk < npg && sub == 1) {
+                    bool need = false, bad = false, wide = false;
+#pragma unroll
+                    for (int t = 0; t < 3; ++t)
+#pragma unroll
+                        for (int v = 0; v < 4; ++v) {
+                            const int i = (t == 2 ? 16 : 0) + grp + 4 * v, j = (t == 0 ? 0 : 16) + i16;
+                            const double hii = L.diag[wk][s_pos0[i]], hjj = L.diag[wk][s_pos0[j]];
+                            const double hij = acc[t][v];
+                            bad = bad || !(fabs(hij) <= 0x1.fffffffffffffp+1023);
+                            need = need || (i < j && !(hij * hij <= tol2 * hii * hjj));
+                            wide = wide || (i < j && !in_trig_range_bits(hii, hjj));
+                        }
+                    if (__builtin_amdgcn_ballot_w64(wide)) {
+                        need = false;
 #pragma unroll
                         for (int t = 0; t < 3; ++t)
 #pragma unroll
                             for (int v = 0; v < 4; ++v) {
-                                double *r = red + ((wk * 3 + t) * 4 + v) * 64 + lane;
-                                const double h = (wv == 0) ? acc[t][v] : *r + acc[t][v];
-                                if (wv < 1) {
-                                    *r = h;
-                                } else {
-                                    // tile t: (0,0), (0,1), (1,1); entry (i, j) of H, both
-                                    // triangles; padding columns become unit vectors
-                                    const int i = (t == 2 ? 16 : 0) + grp + 4 * v;
-                                    const int j = (t == 0 ? 0 : 16) + i16;
-                                    const bool ok = pair_col(i, kBlkW, pq) < n && pair_col(j, kBlkW, pq) < n;
-                                    const double hv = ok ? h : (i == j ? 1.0 : 0.0);
-                                    Rk[j * kBlkLD + i] = hv;
-                                    Rk[i * kBlkLD + j] = hv;
-                                }
-                            }
-                    }
-                    __syncthreads();
-                }
-
-                // (2) which pairs need the inner sweep: some (i, j) fails the
-                // relative orthogonality test on H (reading: <= passes)
-#pragma unroll
-                for (int u = 0; u < kBlkPairs; ++u) {
-                    bool need = false;
-                    if (u < npg) {
-                        const double *Rk = Rm + u * kBlkMat;
-                        for (int e = tid; e < kBlkBW * kBlkBW; e += kBlkThreads) {
-                            const int i = e & 31, j = e >> 5;
-                            if (i < j) {
-                                const double hij = Rk[j * kBlkLD + i];
-                                const double hii = Rk[i * kBlkLD + i], hjj = Rk[j * kBlkLD + j];
-                                need = need || (hij != 0.0 &&
+                                const int i = (t == 2 ? 16 : 0) + grp + 4 * v, j = (t == 0 ? 0 : 16) + i16;
+                                const double hii = L.diag[wk][s_pos0[i]], hjj = L.diag[wk][s_pos0[j]];
+                                const double hij = acc[t][v];
+                                need = need || (i < j && hij != 0.0 &&
                                                 !(fabs(hij) <= tol * sqrt(hii) * sqrt(hjj)));
                             }
-                        }
                     }
-                    if (__ballot(need) != 0ull && lane == 0) atomicOr(&s_need[u], 1);
+                    const bool any_need = __builtin_amdgcn_ballot_w64(need) != 0;
+                    const bool any_bad = __builtin_amdgcn_ballot_w64(bad) != 0;
+                    if (lane == 0 && any_need) {
+                        if (any_bad) s_bad = 1;  // ends the problem after this sweep
+                        else s_need[wk] = 1;
+                    }
                 }
                 __syncthreads();
                 int any = 0;
@@ -236,131 +525,12 @@ __device__ __forceinline__ int blocked_sweeps(double *G, double *V, int m, int n
                 for (int u = 0; u < kBlkPairs; ++u) any |= (u < npg) ? s_need[u] : 0;
                 if (!any) continue;
 
-                // (3) Cholesky H = R^T R (right-looking, unpivoted; Section 4.1),
-                // one wave per pair in two panels of 16 rows: lane j holds rows
-                // 16 kb .. 16 kb + 15 of column j in registers and the pivots and
-                // multipliers are broadcast with readlane (no barrier); between the
-                // panels each lane subtracts the first panel's rows from its column
-                // of the trailing block, reading them from LDS.  Row k of R is H's
-                // row k (as updated) times 1/sqrt(h_kk); a pivot that is not
-                // positive makes row k zero, a NaN or infinite one ends the problem.
-                if (wave < npg && s_need[wave]) {
-                    double *Rk = Rm + wave * kBlkMat;
-                    const int j = lane & 31;
-                    int bad_met = 0;
-#pragma unroll
-                    for (int kb = 0; kb < 2; ++kb) {
-                        if (kb == 1 && j >= 16) {
-                            // H[16 + i][j] -= sum_k R[k][16 + i] R[k][j], k < 16, in k order
-                            for (int i = 0; i <= j - 16; ++i) {
-                                double hv = Rk[j * kBlkLD + 16 + i];
-#pragma unroll
-                                for (int k = 0; k < 16; ++k)
-                                    hv = fma(-Rk[(16 + i) * kBlkLD + k], Rk[j * kBlkLD + k], hv);
-                                Rk[j * kBlkLD + 16 + i] = hv;
-                            }
-                        }
-                        wave_lds_sync();
-                        double hb[16];
-#pragma unroll
-                        for (int i = 0; i < 16; ++i) hb[i] = Rk[j * kBlkLD + 16 * kb + i];
-#pragma unroll
-                        for (int k = 0; k < 16; ++k) {
-                            const int kk = 16 * kb + k;
-                            const double hkk = lane_value(hb[k], kk);
-                            const bool bad = !(fabs(hkk) <= 0x1.fffffffffffffp+1023);
-                            const bool pos = !bad && hkk > 0.0;
-                            bad_met |= bad ? 1 : 0;
-                            double rs, d;
-                            rsqrt_sqrt(pos ? hkk : 1.0, rs, d);
-                            double r = (j == kk) ? d : hb[k] * rs;
-                            r = (pos && j >= kk) ? r : 0.0;
-                            hb[k] = r;
-#pragma unroll
-                            for (int i = k + 1; i < 16; ++i)
-                                hb[i] = fma(-lane_value(r, 16 * kb + i), r, hb[i]);
-                        }
-                        if (lane < kBlkBW) {
-#pragma unroll
-                            for (int i = 0; i < 16; ++i)
-                                Rk[j * kBlkLD + 16 * kb + i] = (j >= 16 * kb + i) ? hb[i] : 0.0;
-                        }
-                        wave_lds_sync();
-                    }
-                    if (lane == 0 && bad_met) s_bad = 1;
-                }
-                for (int e = tid; e < kBlkPairs * kBlkBW * kBlkBW; e += kBlkThreads) {
-                    const int k = e / (kBlkBW * kBlkBW), r = e % kBlkBW, c = (e / kBlkBW) % kBlkBW;
-                    Vm[k * kBlkMat + r * kBlkLD + c] = (r == c) ? 1.0 : 0.0;
-                }
-                __syncthreads();
+                // (3) one inner sweep on H, V' into H's place
+                blk_inner_sweep(L, s_need, s_cmax, s_rotk, prop);
 
-                // (4) one inner sweep on R, 8 lanes per pivot pair (rows x + 8r) on
-                // waves 0-7, V' row-major.  Subphase 2 on squares where they cannot
-                // leave the normal range (h_pq != 0 implies h_pp, h_qq > 0), else
-                // in IEEE operations.
-                {
-                    constexpr int RL = kBlkBW / 8;  // rows per lane
-                    const int gid = tid >> 3, k = gid >> 4, slot2 = gid & 15, x = tid & 7;
-                    const bool act = k < npg && s_need[k];
-                    const double tol2 = kEps * kEps * kBlkBW;  // tol^2, exact
-                    double *Rk = Rm + k * kBlkMat, *Vk = Vm + k * kBlkMat;
-                    for (int st2 = 0; st2 < kBlkBW - 1; ++st2) {
-                        if (act) {
-                            const int p = itbl[st2 * kBlkBW + 2 * slot2];
-                            const int q = itbl[st2 * kBlkBW + 2 * slot2 + 1];
-                            double *rp = Rk + p * kBlkLD, *rq = Rk + q * kBlkLD;
-                            double a[RL], bq[RL];
-#pragma unroll
-                            for (int r = 0; r < RL; ++r) {
-                                a[r] = rp[x + 8 * r];
-                                bq[r] = rq[x + 8 * r];
-                            }
-                            double hpp = a[0] * a[0], hqq = bq[0] * bq[0], hpq = a[0] * bq[0];
-#pragma unroll
-                            for (int r = 1; r < RL; ++r) {
-                                hpp = fma(a[r], a[r], hpp);
-                                hqq = fma(bq[r], bq[r], hqq);
-                                hpq = fma(a[r], bq[r], hpq);
-                            }
-                            hpp = half_row_sum(hpp);
-                            hqq = half_row_sum(hqq);
-                            hpq = half_row_sum(hpq);
-                            double tn = 0.0, cs = 0.0;
-                            bool rot;
-                            if (in_trig_range(hpp, hqq)) {
-                                rot = !(hpq * hpq <= tol2 * hpp * hqq);
-                                bool clamped;
-                                if (rot) rotation_fast(hpp, hqq, hpq, 1, tn, cs, clamped);
-                            } else {
-                                rot = trig_pair(hpp, hqq, hpq, tol, tn, cs);
-                            }
-                            if (rot) {
-#pragma unroll
-                                for (int r = 0; r < RL; ++r) {
-                                    rp[x + 8 * r] = cs * fma(-tn, bq[r], a[r]);
-                                    rq[x + 8 * r] = cs * fma(tn, a[r], bq[r]);
-                                }
-#pragma unroll
-                                for (int r = 0; r < RL; ++r) {
-                                    double *vr = Vk + (x + 8 * r) * kBlkLD;
-                                    const double c0 = vr[p], d0 = vr[q];
-                                    vr[p] = cs * fma(-tn, d0, c0);
-                                    vr[q] = cs * fma(tn, c0, d0);
-                                }
-                                if (x == 0) {
-                                    atomicAdd(&s_rotk[k], 1);
-                                    prop += cs != 1.0 ? 1 : 0;
-                                }
-                            }
-                        }
-                        __syncthreads();
-                    }
-                }
-
-                // (5) [G_p G_q] V' and [V_p V_q] V' for the pairs that rotated
+                // (4) [G_p G_q] V' and [V_p V_q] V' for the pairs that rotated
                 if (wk < npg && s_rotk[wk] > 0) {
-                    const double *vs = Vm + wk * kBlkMat;
+                    const double *vs = L.H[wk];
                     blk_rows_update(G, m, m, pq, n, vs, sub, 2);
                     if (V) blk_rows_update(V, n, n, pq, n, vs, sub, 2);
                 }

@@ -72,6 +72,7 @@ struct jsvd_handle_s {
     std::map<std::pair<int, int>, DeviceTable> quad_tables;   // (order, kind) -> int[8][]
     // batched path: strategy tables of every order up to kBatchMaxN
     void *batch_tables = nullptr;   // uchar pairs
+    const unsigned char *batch_jac = nullptr;  // position_tables' of order 32, in batch_tables
     void *batch_meta = nullptr;     // int tbl_order[kBatchMaxN+1], int64 tbl_off[kBatchMaxN/2+1]
     int cu_count = 0;
     int batch_lds = 0;              // dynamic LDS bytes of the batched kernel
@@ -464,6 +465,7 @@ int solve(jsvd_handle_s *h, int64_t m, int64_t n, double *A, int64_t lda, double
     a.btbl_off = reinterpret_cast<const int64_t *>(
         static_cast<char *>(h->batch_meta) + align_up((kBatchMaxN + 1) * sizeof(int), 256));
     a.btbls = static_cast<const unsigned char *>(h->batch_tables);
+    a.bjac = h->batch_jac;
     a.quads = nullptr;
     a.next_pairs = nullptr;
     if (bw == 128 && !h->batch_tables) return JSVD_HIP_ERROR;
@@ -1035,7 +1037,6 @@ int ensure_batch_tables(jsvd_handle_s *h) {
         if (strategy_order(N) != N) continue;
         Table t;
         if (!make_table(N, JSVD_STRAT_RREV, t)) return JSVD_HIP_ERROR;
-        if (N == kBatchInnerOrder) order_for_banks(t);  // the blocked method's inner sweeps
         tbl_off[N / 2] = (int64_t)flat.size();
         for (const auto &stp : t)
             for (const auto &pr : stp) {
@@ -1044,6 +1045,12 @@ int ensure_batch_tables(jsvd_handle_s *h) {
             }
     }
     for (int k = 1; k <= kBatchMaxN; ++k) tbl_order[k] = strategy_order(k);
+    // the blocked method's inner sweeps
+    flat.resize(align_up(flat.size(), 16));
+    const size_t jac_off = flat.size();
+    Table inner;
+    if (!make_table(kBatchInnerOrder, JSVD_STRAT_RREV, inner)) return JSVD_HIP_ERROR;
+    position_tables(inner, flat);
     void *tables = nullptr, *meta = nullptr;
     const size_t meta_bytes =
         align_up(tbl_order.size() * sizeof(int), 256) + tbl_off.size() * sizeof(int64_t);
@@ -1053,6 +1060,7 @@ int ensure_batch_tables(jsvd_handle_s *h) {
         return JSVD_NO_MEMORY;
     }
     h->batch_tables = tables;
+    h->batch_jac = static_cast<unsigned char *>(tables) + jac_off;
     h->batch_meta = meta;
     HIP_TRY(hipMemcpy(h->batch_tables, flat.data(), flat.size(), hipMemcpyHostToDevice));
     HIP_TRY(hipMemcpy(h->batch_meta, tbl_order.data(), tbl_order.size() * sizeof(int),
@@ -1451,6 +1459,7 @@ int launch_batched_solve(jsvd_handle_s *h, int64_t batch, int32_t max_n, const i
     b.tbl_off = reinterpret_cast<const int64_t *>(
         static_cast<char *>(h->batch_meta) + align_up((kBatchMaxN + 1) * sizeof(int), 256));
     b.tbls = static_cast<const unsigned char *>(h->batch_tables);
+    b.jac = h->batch_jac;
     b.max_sweeps = o.max_sweeps;
     b.status = status;
     b.sweeps = sweeps;

@@ -1009,7 +1009,7 @@ constexpr int kW128Threads = kBlkThreads;
 __global__ __launch_bounds__(kW128Threads) void inner128_kernel(StepArgs a) {
     constexpr int BW = 128, LD = BW + 1, NT = kW128Threads, NWAVES = NT / 64;
     constexpr int EPT = BW * BW / NT;  // Gram entries summed per thread
-    __shared__ double L[BW * LD];      // H, then R; then the block method's R'' and V''
+    __shared__ __align__(16) double L[BW * LD];  // H, then R; then the block method's R'' and V''
     __shared__ int sflag[2];           // [0] NaN or infinite pivot, [1] zero pivots
     __shared__ int stats[3];           // rotations, proper rotations, sub-pair updates
     static_assert(kBlkLdsDoubles <= BW * LD, "the block method's LDS fits in L");
@@ -1181,7 +1181,7 @@ __global__ __launch_bounds__(kW128Threads) void inner128_kernel(StepArgs a) {
     }
     __syncthreads();
     const int r = blocked_sweeps(Rg, Vg, BW, BW, max(1, min(a.max_inner_sweeps, 0xffff)),
-                                 a.btbl_order, a.btbl_off, a.btbls, L, stats);
+                                 a.btbl_order, a.btbl_off, a.btbls, a.bjac, L, stats);
     __syncthreads();
     if (tid == 0) {
         if (r & kBlkNonfinite) {

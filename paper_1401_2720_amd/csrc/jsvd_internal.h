@@ -104,6 +104,7 @@ struct StepArgs {
     const int *btbl_order;
     const int64_t *btbl_off;
     const unsigned char *btbls;
+    const unsigned char *bjac;  // position_tables' of order 32
     // the update fused with the next p-step's Gram kernel: the quads of this
     // p-step (8 ints each: old pairs ia, ib, new pairs jx, jy, blocks a0 of
     // ia and b0 of ib that go to jx, two unused) and the next p-step's pairs
@@ -120,7 +121,7 @@ hipError_t launch_fused(int nquads, const StepArgs &a, hipStream_t s);
 // ------------------------------------------------------ batched small SVDs
 constexpr int kBatchMaxN = 256;  // largest n of a problem in the batched path
 constexpr int kBatchBlockMinN = 65;     // built-in: batched problems with n >= this are blocked
-constexpr int kBatchBlockLds = 8448;   // doubles of LDS the blocked method needs
+constexpr int kBatchBlockLds = 9512;   // doubles of LDS the blocked method needs
 constexpr int kBatchInnerOrder = 32;   // 2w of the blocked method's inner sweeps
 
 struct BatchArgs {
@@ -133,6 +134,7 @@ struct BatchArgs {
     const int *tbl_order;                       // device [kBatchMaxN + 1]: strategy order for n
     const int64_t *tbl_off;                     // device: offset of the order-N table at [N/2]
     const unsigned char *tbls;                  // device: concatenated zero-based pair tables
+    const unsigned char *jac;                   // device: position_tables' of order 32
     int max_sweeps;
     int32_t *status, *sweeps;                   // device, per problem (may be null)
     int64_t lds_doubles;                        // problems with m n <= this work in LDS

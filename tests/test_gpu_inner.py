@@ -99,3 +99,22 @@ def test_nonfinite(value):
     with pytest.raises(jsvd.JsvdError) as e:
         jsvd.gesvd(torch.from_numpy(A).cuda(), qr="off", scaled="off")
     assert e.value.code == 3
+
+
+# the batched path's blocked method: one block pair and its padding, odd and
+# even block counts, the largest n; columns that repeat; a NaN in one problem
+@pytest.mark.parametrize("n", [33, 47, 48, 49, 64, 65, 96, 97, 130, 256])
+def test_batched_blocked_edges(n):
+    torch, jsvd = _jsvd()
+    g = np.random.default_rng(n)
+    mats = [g.standard_normal((n + k, n)) for k in (0, 1, 17)]
+    mats[1][:, n // 2:2 * (n // 2)] = mats[1][:, :n // 2]
+    bad = g.standard_normal((n, n))
+    bad[3, 2] = np.nan
+    b = jsvd.Batch(mats + [bad])
+    jsvd.gesvd_batched(b)
+    torch.cuda.synchronize()
+    assert b.status.tolist() == [0, 0, 0, 3]
+    for i, A in enumerate(mats):
+        U, S, V = b.results(i)
+        _check(A, U, S, V, np.linalg.svd(A, compute_uv=False))
