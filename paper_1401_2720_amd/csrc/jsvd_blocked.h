@@ -64,7 +64,17 @@ __device__ __forceinline__ bool trig_pair(double hpp, double hqq, double hpq, do
 // other's latencies.
 constexpr int kBlkW = 16, kBlkBW = 2 * kBlkW, kBlkLD = kBlkBW + 1, kBlkPairs = 4;
 constexpr int kBlkThreads = 512;  // 8 waves: two per pivot pair in the Gram and update phases
+typedef double d2a __attribute__((ext_vector_type(2), aligned(8)));  // a 16-byte load
 constexpr int kBlkMat = kBlkBW * kBlkLD;  // doubles of one H or V'
+
+// The lane number, opaque to the compiler, so that what is computed from it
+// is computed where it is used: hoisted out of the group loop, the addresses
+// of all phases together spill (128 registers).
+__device__ __forceinline__ int fresh_lane() {
+    int lane = threadIdx.x & 63;
+    asm volatile("" : "+v"(lane));
+    return lane;
+}
 
 // X[0:rows, cols of pq] <- X[0:rows, cols of pq] V' for the rows of one
 // wave (16-row slices from row 16 sub, stride 16 nsub), V' row-major in LDS
@@ -72,18 +82,24 @@ constexpr int kBlkMat = kBlkBW * kBlkLD;  // doubles of one H or V'
 __device__ __forceinline__ void blk_rows_update(double *X, int ldx, int rows, int2 pq, int n,
                                                 const double *vs, int sub, int nsub) {
     constexpr int KS = kBlkBW / 4;
-    const int lane = threadIdx.x & 63, i16 = lane & 15, grp = lane >> 4;
+    const int lane = fresh_lane(), i16 = lane & 15, grp = lane >> 4;
+    auto load = [&](int base, double (&bx)[KS]) __attribute__((always_inline)) {
+        const int row = base + i16;
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) {
+            const int gc = (int)pair_col(4 * ks + grp, kBlkW, pq);
+            bx[ks] = (row < rows && gc < n) ? X[gc * ldx + row] : 0.0;
+        }
+    };
+    double bx[KS];
+    if (16 * sub < rows) load(16 * sub, bx);
     for (int base = 16 * sub; base < rows; base += 16 * nsub) {
         // V' is re-read from LDS in every slice rather than held in registers
         asm volatile("" ::: "memory");
         const int row = base + i16;
         const bool rv = row < rows;
-        double bx[KS];
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-            const int gc = (int)pair_col(4 * ks + grp, kBlkW, pq);
-            bx[ks] = (rv && gc < n) ? X[gc * ldx + row] : 0.0;
-        }
+        double by[KS] = {};
+        if (base + 16 * nsub < rows) load(base + 16 * nsub, by);
 #pragma unroll
         for (int jt = 0; jt < kBlkBW / 16; ++jt) {
             d4 acc = d4{0.0, 0.0, 0.0, 0.0};
@@ -96,6 +112,8 @@ __device__ __forceinline__ void blk_rows_update(double *X, int ldx, int rows, in
                 if (rv && gc < n) X[gc * ldx + row] = acc[v];
             }
         }
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) bx[ks] = by[ks];
     }
 }
 
@@ -122,6 +140,9 @@ static_assert(3 * 4 * 64 <= 2 * kBlkW * kBlkBW, "Gram partial sums fit in xch");
 static_assert(kBlkLdsDoubles == kBatchBlockLds, "host LDS bound of the blocked method");
 static_assert(kBlkBW == kBatchInnerOrder && kBlkPairs == 4 && kBlkThreads == 512, "wave roles");
 
+// pair bytes of the largest block strategy (order 16)
+constexpr int kBlkMaxTable = (kBatchMaxN / kBlkW - 1) * (kBatchMaxN / kBlkW);
+static_assert(kBlkMaxTable <= kBlkThreads, "one pair byte per thread");
 constexpr int kBlkConverged = 1 << 16, kBlkNonfinite = 1 << 17;
 
 // Wave 0 of blk_inner_sweep: lane 16 mx + k has pair k of matrix mx.
@@ -138,7 +159,7 @@ struct BlkRotations {
     int rots = 0, prop = 0;
 
     __device__ __forceinline__ BlkRotations(BlkLds &lds, int lane, const int *need, const int *cmax)
-        : L(lds), mx(lane / NP), k(lane % NP), cm(cmax[lane / NP]), act(need[lane / NP] != 0) {}
+        : L(lds), mx(lane / NP), k(lane % NP), cm(cmax[lane / NP]), act(need[lane / NP] == 1) {}
 
     template <int PAR>
     static __device__ __forceinline__ unsigned at(unsigned x8, unsigned y8) {
@@ -260,7 +281,7 @@ __device__ __forceinline__ void blk_rotate_v(BlkLds &L, int m, int sl, int vrow,
     }
 }
 
-// One inner sweep on the matrices k with need[k] (H and diag set); V' into
+// One inner sweep on the matrices k with need[k] == 1 (H and diag set); V' into
 // H, row-major; their rotations added to rotk, the proper ones of this lane
 // to prop.  cmax[k]: columns of pair k from there on are padding.  All 512
 // threads; each role has its own loop, with the same barriers.
@@ -268,7 +289,7 @@ __device__ __forceinline__ void blk_inner_sweep(BlkLds &L, const int *need, cons
                                                 int *rotk, int &prop) {
     constexpr int NP = kBlkW, NS = kBlkBW - 1, LD = kBlkLD;
     static_assert(NS % 2 == 1, "the last step is an even one");
-    const int lane = threadIdx.x & 63;
+    const int lane = fresh_lane();
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     if (wave == 0) {
         __builtin_amdgcn_s_setprio(3);
@@ -300,12 +321,15 @@ __device__ __forceinline__ void blk_inner_sweep(BlkLds &L, const int *need, cons
             bJ[u] = first ? g + 1 + l : l;
         }
         const int m = wave - 1;
+        const bool on = need[m] == 1, on3 = wave < 3 && need[3] == 1;
         const int I3 = wave == 2 ? bI[1] : bI[0], J3 = wave == 2 ? bJ[1] : bJ[0];
         auto step = [&](auto par) __attribute__((always_inline)) {
             constexpr int PAR = decltype(par)::value;
-            blk_rotate_block<PAR>(L, m, bI[0], bJ[0]);
-            blk_rotate_block<PAR>(L, m, bI[1], bJ[1]);
-            if (wave < 3) blk_rotate_block<PAR>(L, 3, I3, J3);
+            if (on) {
+                blk_rotate_block<PAR>(L, m, bI[0], bJ[0]);
+                blk_rotate_block<PAR>(L, m, bI[1], bJ[1]);
+            }
+            if (on3) blk_rotate_block<PAR>(L, 3, I3, J3);
             __syncthreads();
         };
         __syncthreads();
@@ -317,6 +341,7 @@ __device__ __forceinline__ void blk_inner_sweep(BlkLds &L, const int *need, cons
     } else {
         // matrix vm, slots 4 u + lane / 16, two rows per lane
         const int vm = wave == 4 ? 3 : wave - 5, vrow = 2 * (lane % NP), vq = lane / NP;
+        const bool on = need[vm] == 1;
         double2 vk[4], vr[4];
         unsigned ctl[4];
         auto kept_col = [&](int e, int &ck, int &cr) __attribute__((always_inline)) {
@@ -328,7 +353,7 @@ __device__ __forceinline__ void blk_inner_sweep(BlkLds &L, const int *need, cons
         auto step = [&](auto par, int st) __attribute__((always_inline)) {
 #pragma unroll
             for (int u = 0; u < 4; ++u)
-                blk_rotate_v<decltype(par)::value>(L, vm, 4 * u + vq, vrow, st, vk[u], vr[u], ctl[u]);
+                if (on) blk_rotate_v<decltype(par)::value>(L, vm, 4 * u + vq, vrow, st, vk[u], vr[u], ctl[u]);
             __syncthreads();
         };
 #pragma unroll
@@ -374,10 +399,9 @@ __device__ __forceinline__ int blocked_sweeps(double *G, double *V, int m, int n
                                               double *lds, int *stats = nullptr) {
     __shared__ int2 s_pq[kBlkPairs];
     __shared__ int s_need[kBlkPairs], s_rotk[kBlkPairs], s_cmax[kBlkPairs], s_prop, s_bad;
-    __shared__ unsigned char s_pos0[kBlkBW];
+    __shared__ unsigned char s_pos0[kBlkBW], s_row[kBlkMaxTable];
     BlkLds &L = *reinterpret_cast<BlkLds *>(lds);
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int i16 = lane & 15, grp = lane >> 4;
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int nb = (n + kBlkW - 1) / kBlkW;
     const int NB = tbl_order[nb];
     const unsigned char *btbl = tbls + tbl_off[NB >> 1];
@@ -395,6 +419,7 @@ __device__ __forceinline__ int blocked_sweeps(double *G, double *V, int m, int n
         L.vctl[tid] = (t.y >> 24) * (kBlkBW * 8) | (t.y & 0x20000u) << 14 | (t.y & 0x40000u) << 12;
     }
     if (tid < kBlkBW) s_pos0[tid] = jac[8 * kEntries + tid];
+    if (tid < (NB - 1) * NB) s_row[tid] = btbl[tid];  // the block strategy
 
     int sweeps = 0, result = 0;
     if (tid == 0) s_bad = 0;
@@ -402,7 +427,7 @@ __device__ __forceinline__ int blocked_sweeps(double *G, double *V, int m, int n
         if (tid == 0) s_prop = 0;
         int prop = 0;  // proper rotations of this lane's pivot pairs (wave 0)
         for (int st = 0; st < NB - 1; ++st) {
-            const unsigned char *row = btbl + (size_t)st * NB;
+            const unsigned char *row = s_row + st * NB;
             int slot = 0;
             for (;;) {
                 // the next pivot pairs of the step with a block inside the
@@ -420,61 +445,94 @@ __device__ __forceinline__ int blocked_sweeps(double *G, double *V, int m, int n
                 if (npg == 0) break;
                 if (tid < kBlkPairs) s_need[tid] = s_rotk[tid] = 0;
                 __syncthreads();
+                const int lane = fresh_lane(), i16 = lane & 15, grp = lane >> 4;
 
-                // (1) Gram matrices: each wave sums its 16-row slices; the two
-                // partial sums of a pair are added in wave order.
+                // (1) Gram matrices: each wave sums its 16-row slices, the next
+                // slice's loads issued before the products of the current one;
+                // the two partial sums of a pair are added in wave order.
+                // positions of the columns i and j of this lane's entries of H
+                int pos_i[2][2], pos_j[2];
+#pragma unroll
+                for (int t = 0; t < 2; ++t) {
+#pragma unroll
+                    for (int v = 0; v < 2; ++v) pos_i[t][v] = s_pos0[16 * t + grp + 4 * (v + 2 * sub)];
+                    pos_j[t] = s_pos0[16 * t + i16];
+                }
                 d4 acc[3];
 #pragma unroll
                 for (int t = 0; t < 3; ++t) acc[t] = d4{0.0, 0.0, 0.0, 0.0};
                 int2 pq = make_int2(0, 0);
-                bool valid[2] = {false, false};
+                double *const red = &L.xch[wk][0][0];
                 if (wk < npg) {
                     pq = s_pq[wk];
                     const double *col[2];
+                    bool valid[2];
 #pragma unroll
                     for (int t = 0; t < 2; ++t) {
-                        const int64_t gc = pair_col(16 * t + i16, kBlkW, pq);
+                        const int gc = (int)pair_col(16 * t + i16, kBlkW, pq);
                         valid[t] = gc < n;
-                        col[t] = G + (valid[t] ? gc : 0) * m;
+                        col[t] = G + (valid[t] ? gc : 0) * m + 4 * grp;
                     }
+                    const bool allv = (pq.y + 1) * kBlkW <= n;
+                    auto load = [&](int base, double (&x)[2][4]) __attribute__((always_inline)) {
+                        if (allv && base + 16 <= m) {
+#pragma unroll
+                            for (int t = 0; t < 2; ++t)
+#pragma unroll
+                                for (int s2 = 0; s2 < 2; ++s2) {
+                                    const d2a v = *reinterpret_cast<const d2a *>(col[t] + base + 2 * s2);
+                                    x[t][2 * s2] = v.x;
+                                    x[t][2 * s2 + 1] = v.y;
+                                }
+                        } else {
+#pragma unroll
+                            for (int t = 0; t < 2; ++t)
+#pragma unroll
+                                for (int s2 = 0; s2 < 4; ++s2)
+                                    x[t][s2] = (valid[t] && base + 4 * grp + s2 < m) ? col[t][base + s2] : 0.0;
+                        }
+                    };
+                    double x[2][4];
+                    if (16 * sub < m) load(16 * sub, x);
                     for (int base = 16 * sub; base < m; base += 32) {
-                        const int rb = base + 4 * grp;
-                        double x[2][4];
-#pragma unroll
-                        for (int t = 0; t < 2; ++t)
-#pragma unroll
-                            for (int s2 = 0; s2 < 4; ++s2)
-                                x[t][s2] = (valid[t] && rb + s2 < m) ? col[t][rb + s2] : 0.0;
+                        double y[2][4] = {};
+                        if (base + 32 < m) load(base + 32, y);
 #pragma unroll
                         for (int s2 = 0; s2 < 4; ++s2) {
                             acc[0] = mfma16(x[0][s2], x[0][s2], acc[0]);
                             acc[1] = mfma16(x[0][s2], x[1][s2], acc[1]);
                             acc[2] = mfma16(x[1][s2], x[1][s2], acc[2]);
                         }
+#pragma unroll
+                        for (int t = 0; t < 2; ++t)
+#pragma unroll
+                            for (int s2 = 0; s2 < 4; ++s2) x[t][s2] = y[t][s2];
                     }
-                }
-                double *const red = &L.xch[wk][0][0];
-                if (wk < npg && sub == 0) {
+                    // each wave passes on the half that the other one sums
 #pragma unroll
                     for (int t = 0; t < 3; ++t)
 #pragma unroll
-                        for (int v = 0; v < 4; ++v) red[(t * 4 + v) * 64 + lane] = acc[t][v];
+                        for (int v = 0; v < 2; ++v)
+                            red[(6 * sub + 2 * t + v) * 64 + lane] = sub ? acc[t][v] : acc[t][v + 2];
                 }
                 __syncthreads();
-                // entry (i, j), i <= j, of H to its place; padding columns become
-                // unit vectors
-                if (wk < npg && sub == 1) {
+                // entries (i, j), i <= j, of H to their places, v = 0, 1 by the
+                // first wave, 2, 3 by the second; padding columns become unit vectors
+                double hs[3][2];
+                if (wk < npg) {
 #pragma unroll
                     for (int t = 0; t < 3; ++t)
 #pragma unroll
-                        for (int v = 0; v < 4; ++v) {
-                            const int i = (t == 2 ? 16 : 0) + grp + 4 * v, j = (t == 0 ? 0 : 16) + i16;
+                        for (int v = 0; v < 2; ++v) {
+                            const double o = red[(6 * (1 - sub) + 2 * t + v) * 64 + lane];
+                            const double h = sub ? o + acc[t][v + 2] : acc[t][v] + o;
+                            const int i = (t == 2 ? 16 : 0) + grp + 4 * (v + 2 * sub);
+                            const int j = (t == 0 ? 0 : 16) + i16;
                             const bool ok = pair_col(i, kBlkW, pq) < n && pair_col(j, kBlkW, pq) < n;
-                            const double h = red[(t * 4 + v) * 64 + lane] + acc[t][v];
-                            acc[t][v] = ok ? h : (i == j ? 1.0 : 0.0);
-                            const int pi = s_pos0[i], pj = s_pos0[j];
-                            if (i < j) L.H[wk][min(pi, pj) * kBlkLD + max(pi, pj)] = acc[t][v];
-                            if (i == j) L.diag[wk][pi] = acc[t][v];
+                            hs[t][v] = ok ? h : (i == j ? 1.0 : 0.0);
+                            const int pi = pos_i[t == 2][v], pj = pos_j[t != 0];
+                            if (i < j) L.H[wk][min(pi, pj) * kBlkLD + max(pi, pj)] = hs[t][v];
+                            if (i == j) L.diag[wk][pi] = hs[t][v];
                         }
                     if (lane == 0) {
                         const int nq = n - pq.y * kBlkW;
@@ -486,43 +544,45 @@ __device__ __forceinline__ int blocked_sweeps(double *G, double *V, int m, int n
                 // (2) which pairs need the inner sweep: some (i, j) fails the
                 // relative orthogonality test on H (reading: <= passes), on
                 // squares where they cannot leave the normal range
-                if (wk < npg && sub == 1) {
+                if (wk < npg) {
                     bool need = false, bad = false, wide = false;
 #pragma unroll
                     for (int t = 0; t < 3; ++t)
 #pragma unroll
-                        for (int v = 0; v < 4; ++v) {
-                            const int i = (t == 2 ? 16 : 0) + grp + 4 * v, j = (t == 0 ? 0 : 16) + i16;
-                            const double hii = L.diag[wk][s_pos0[i]], hjj = L.diag[wk][s_pos0[j]];
-                            const double hij = acc[t][v];
-                            bad = bad || !(fabs(hij) <= 0x1.fffffffffffffp+1023);
-                            need = need || (i < j && !(hij * hij <= tol2 * hii * hjj));
-                            wide = wide || (i < j && !in_trig_range_bits(hii, hjj));
+                        for (int v = 0; v < 2; ++v) {
+                            const bool up = (t == 2 ? 16 : 0) + grp + 4 * (v + 2 * sub) < (t == 0 ? 0 : 16) + i16;
+                            const double hii = L.diag[wk][pos_i[t == 2][v]], hjj = L.diag[wk][pos_j[t != 0]];
+                            bad = bad || !(fabs(hs[t][v]) <= 0x1.fffffffffffffp+1023);
+                            need = need || (up && !(hs[t][v] * hs[t][v] <= tol2 * hii * hjj));
+                            wide = wide || (up && !in_trig_range_bits(hii, hjj));
                         }
                     if (__builtin_amdgcn_ballot_w64(wide)) {
                         need = false;
 #pragma unroll
                         for (int t = 0; t < 3; ++t)
 #pragma unroll
-                            for (int v = 0; v < 4; ++v) {
-                                const int i = (t == 2 ? 16 : 0) + grp + 4 * v, j = (t == 0 ? 0 : 16) + i16;
-                                const double hii = L.diag[wk][s_pos0[i]], hjj = L.diag[wk][s_pos0[j]];
-                                const double hij = acc[t][v];
-                                need = need || (i < j && hij != 0.0 &&
-                                                !(fabs(hij) <= tol * sqrt(hii) * sqrt(hjj)));
+                            for (int v = 0; v < 2; ++v) {
+                                const bool up = (t == 2 ? 16 : 0) + grp + 4 * (v + 2 * sub) < (t == 0 ? 0 : 16) + i16;
+                                const double hii = L.diag[wk][pos_i[t == 2][v]], hjj = L.diag[wk][pos_j[t != 0]];
+                                need = need || (up && hs[t][v] != 0.0 &&
+                                                !(fabs(hs[t][v]) <= tol * sqrt(hii) * sqrt(hjj)));
                             }
                     }
                     const bool any_need = __builtin_amdgcn_ballot_w64(need) != 0;
                     const bool any_bad = __builtin_amdgcn_ballot_w64(bad) != 0;
-                    if (lane == 0 && any_need) {
-                        if (any_bad) s_bad = 1;  // ends the problem after this sweep
-                        else s_need[wk] = 1;
-                    }
+                    if (lane == 0 && (any_need || any_bad))
+                        atomicOr(&s_need[wk], (any_need ? 1 : 0) | (any_bad ? 2 : 0));
                 }
                 __syncthreads();
                 int any = 0;
 #pragma unroll
-                for (int u = 0; u < kBlkPairs; ++u) any |= (u < npg) ? s_need[u] : 0;
+                for (int u = 0; u < kBlkPairs; ++u) {
+                    const int f = u < npg ? s_need[u] : 0;
+                    any |= f == 1;
+                    // a NaN or infinity in a pair that is not left alone ends the
+                    // problem after this sweep
+                    if (tid == 0 && f == 3) s_bad = 1;
+                }
                 if (!any) continue;
 
                 // (3) one inner sweep on H, V' into H's place
