@@ -389,7 +389,7 @@ __device__ __forceinline__ void finish_problem(const BatchArgs &b, int id, int m
     __syncthreads();
 }
 
-// Problems at positions [queue[2], count) of the work order: the pointwise
+// Problems at positions [queue[2], queue[4]) of the work order: the pointwise
 // method, G in LDS when it fits, V in what LDS is left.  DD: DDRJAC pairs
 // and DRDSSQ norms.
 template <bool DD>
@@ -405,13 +405,14 @@ __global__ __launch_bounds__(kBatchThreads) void batched_kernel(BatchArgs b) {
     __shared__ int s_ex[DD ? kBatchMaxN : 1];       // DRDSSQ pairs of the final columns
     __shared__ double s_rt[DD ? kBatchMaxN : 1];
     const int tid = threadIdx.x;
+    const int last = b.queue[4];
 
     for (;;) {
         if (tid == 0) s_item = atomicAdd(&b.queue[1], 1);
         __syncthreads();
         const int item = s_item;
         __syncthreads();
-        if (item >= b.count) break;  // every workgroup leaves once the queue is drained
+        if (item >= last) break;  // every workgroup leaves once the queue is drained
         const int id = b.order[item];
         const int m = b.m[id], n = b.n[id];
         double *G = b.A + b.a_off[id];
@@ -453,6 +454,233 @@ __global__ __launch_bounds__(kBatchThreads) void batched_kernel(BatchArgs b) {
     }
 }
 
+// ------------------------------------------------------------ one wave each
+// Small problems (wave_fits: n <= 32 and G and V within wave_lds doubles): the
+// pointwise method with a whole problem in one wave and its LDS, so that a CU
+// works on up to 32 problems at once and no step waits for a barrier.  (One
+// 1024-thread workgroup per problem spends a step of a 20 x 12 problem on 12
+// of its 32 half waves and two barriers: 20000 of them took 5.9 ms.)  L lanes
+// per pivot pair, L the largest power of two with 64 / L >= pairs per step;
+// lane x owns rows x, x + L, ... of the pair's columns.  The steps, the test,
+// the rotations and the stopping rule are pointwise_sweeps'; the rotation is
+// rotation_h where its range holds.
+template <int L>
+__device__ __forceinline__ double lanes_sum(double v) {
+    if constexpr (L == 32) return hw_sum(v);
+    v += dpp_mov<0xB1>(v);                          // quad_perm [1,0,3,2]
+    v += dpp_mov<0x4E>(v);                          // quad_perm [2,3,0,1]
+    if constexpr (L >= 8) v += dpp_mov<0x141>(v);   // row_half_mirror
+    if constexpr (L >= 16) v += dpp_mov<0x140>(v);  // row_mirror
+    return v;
+}
+
+// The sweep loop; R > 0: a lane's R rows stay in registers between the dot
+// products and the update (m <= L R); R = 0: any m.  Returns the sweeps, plus
+// kBlkConverged.
+template <int L, int R>
+__device__ int wave_sweeps(double *G, double *V, int m, int n, int N, const unsigned char *tbl,
+                           int max_sweeps) {
+    constexpr int VR = L == 4 ? 8 : L == 8 ? 2 : 1;  // rows of V per lane (n <= N <= 128 / L)
+    const int lane = threadIdx.x, x = lane % L, slot = lane / L;
+    const int half = N >> 1;
+    const double tol = kEps * sqrt((double)m), tol2 = kEps * kEps * m;  // c(eps), squared exact
+    const unsigned short *pairs = reinterpret_cast<const unsigned short *>(tbl);
+    const bool in = slot < half;
+    int sweeps = 0;
+    unsigned nxt = in ? pairs[slot] : 0xff00u;
+    while (sweeps < max_sweeps) {
+        unsigned long long any = 0;  // lanes whose pair rotated properly in the sweep
+        for (int st = 0; st < N - 1; ++st) {
+            const int p = nxt & 0xff, q = nxt >> 8;
+            const bool use = in && q < n;  // no pair, or a padding index
+            const int sn = st + 2 < N ? st + 1 : 0;
+            nxt = in ? pairs[sn * half + slot] : 0xff00u;
+            double *gp = G + (use ? p : 0) * m + x, *gq = G + (use ? q : 0) * m + x;
+            double a[R > 0 ? R : 1], b[R > 0 ? R : 1];
+            double hpp = 0.0, hqq = 0.0, hpq = 0.0;
+            if constexpr (R > 0) {
+#pragma unroll
+                for (int r = 0; r < R; ++r) {
+                    const bool row = x + L * r < m;
+                    a[r] = row ? gp[L * r] : 0.0;
+                    b[r] = row ? gq[L * r] : 0.0;
+                }
+#pragma unroll
+                for (int r = 0; r < R; ++r) {
+                    hpp = fma(a[r], a[r], hpp);
+                    hqq = fma(b[r], b[r], hqq);
+                    hpq = fma(a[r], b[r], hpq);
+                }
+            } else {
+                for (int i = 0; x + i < m; i += L) {
+                    const double a0 = gp[i], b0 = gq[i];
+                    hpp = fma(a0, a0, hpp);
+                    hqq = fma(b0, b0, hqq);
+                    hpq = fma(a0, b0, hpq);
+                }
+            }
+            hpp = lanes_sum<L>(hpp);
+            hqq = lanes_sum<L>(hqq);
+            hpq = lanes_sum<L>(hpq);
+            bool rot = !(hpq * hpq <= tol2 * hpp * hqq);
+            double tn, cs;
+            bool clamped;
+            rotation_h(hpp, hqq, hpq, false, tn, cs, clamped);
+            if (!in_trig_range_bits(hpp, hqq)) rot = trig_pair(hpp, hqq, hpq, tol, tn, cs);
+            rot = rot && use;
+            any |= __builtin_amdgcn_ballot_w64(rot && cs != 1.0);
+            if (rot) {
+                // (4.1); cs == 1 multiplies exactly
+                if constexpr (R > 0) {
+#pragma unroll
+                    for (int r = 0; r < R; ++r)
+                        if (x + L * r < m) {
+                            gp[L * r] = cs * fma(-tn, b[r], a[r]);
+                            gq[L * r] = cs * fma(tn, a[r], b[r]);
+                        }
+                } else {
+                    for (int i = 0; x + i < m; i += L) {
+                        const double a0 = gp[i], b0 = gq[i];
+                        gp[i] = cs * fma(-tn, b0, a0);
+                        gq[i] = cs * fma(tn, a0, b0);
+                    }
+                }
+                if (V) {
+                    double *vp = V + p * n + x, *vq = V + q * n + x;
+                    double c[VR], d[VR];
+#pragma unroll
+                    for (int r = 0; r < VR; ++r) {
+                        const bool row = x + L * r < n;
+                        c[r] = row ? vp[L * r] : 0.0;
+                        d[r] = row ? vq[L * r] : 0.0;
+                    }
+#pragma unroll
+                    for (int r = 0; r < VR; ++r)
+                        if (x + L * r < n) {
+                            vp[L * r] = cs * fma(-tn, d[r], c[r]);
+                            vq[L * r] = cs * fma(tn, c[r], d[r]);
+                        }
+                }
+            }
+            wave_lds_sync();
+        }
+        ++sweeps;
+        if (any == 0) return sweeps | kBlkConverged;
+    }
+    return sweeps;
+}
+
+// The end of a problem, as finish_problem: sigma, the order (non-increasing,
+// ties by index, NaN last), U, V, status and sweeps.
+template <int L>
+__device__ __forceinline__ void wave_finish(const BatchArgs &b, int id, int m, int n, double *G,
+                                            double *V, const double *Gw, const double *Vw,
+                                            int sweeps, double *sig, int *perm) {
+    const int lane = threadIdx.x, x = lane % L;
+    for (int j0 = 0; j0 < n; j0 += 64 / L) {
+        const int j = j0 + lane / L;
+        double s = 0.0;
+        if (j < n)
+            for (int i = x; i < m; i += L) s = fma(Gw[j * m + i], Gw[j * m + i], s);
+        s = lanes_sum<L>(s);
+        if (j < n && x == 0) sig[j] = sqrt(s);
+    }
+    wave_lds_sync();
+    if (lane < n) {
+        const double kj = sig[lane] != sig[lane] ? -INFINITY : sig[lane];
+        int r = 0;
+        for (int i = 0; i < n; ++i) {
+            const double ki = sig[i] != sig[i] ? -INFINITY : sig[i];
+            r += (ki > kj || (ki == kj && i < lane)) ? 1 : 0;
+        }
+        perm[r] = lane;
+    }
+    wave_lds_sync();
+    // column k and row i of element e = lane, lane + 64, ...
+    auto walk = [&](int rows, auto &&f) {
+        const int dk = 64 / rows, di = 64 % rows;
+        int k = lane / rows, i = lane % rows;
+        for (int e = lane; e < rows * n; e += 64) {
+            f(e, perm[k], i);
+            k += dk;
+            i += di;
+            if (i >= rows) {
+                i -= rows;
+                ++k;
+            }
+        }
+    };
+    walk(m, [&](int e, int c, int i) {
+        const double sg = sig[c];
+        G[e] = sg > 0.0 ? Gw[c * m + i] / sg : 0.0;
+    });
+    if (V) walk(n, [&](int e, int c, int i) { V[e] = Vw[c * n + i]; });
+    if (lane < n) b.S[b.s_off[id] + lane] = sig[perm[lane]];
+    if (lane == 0) {
+        if (b.status) b.status[id] = (sweeps & kBlkConverged) ? 0 : JSVD_NOT_CONVERGED;
+        if (b.sweeps) b.sweeps[id] = sweeps & 0xffff;
+    }
+    wave_lds_sync();
+}
+
+template <int L>
+__device__ __forceinline__ void wave_problem(const BatchArgs &b, int id, int m, int n, int N,
+                                             double *Gw, double *sig, int *perm) {
+    // rows per lane that stay in registers: up to 64 rows, in two steps
+    constexpr int R1 = L == 4 ? 8 : L == 8 ? 4 : 2, R2 = L >= 16 ? 64 / L : 2 * R1;
+    const int lane = threadIdx.x;
+    double *G = b.A + b.a_off[id];
+    double *V = b.V ? b.V + b.v_off[id] : nullptr;
+    double *Vw = V ? Gw + m * n : nullptr;
+    for (int e = lane; e < m * n; e += 64) Gw[e] = G[e];
+    if (V) {
+        for (int e = lane; e < n * n; e += 64) Vw[e] = 0.0;
+        wave_lds_sync();
+        if (lane < n) Vw[lane * n + lane] = 1.0;
+    }
+    wave_lds_sync();
+    const unsigned char *tbl = b.tbls + b.tbl_off[N >> 1];
+    const int ms = min(b.max_sweeps, 0xffff);
+    int r;
+    if (m <= L * R1)
+        r = wave_sweeps<L, R1>(Gw, Vw, m, n, N, tbl, ms);
+    else if (m <= L * R2)
+        r = wave_sweeps<L, R2>(Gw, Vw, m, n, N, tbl, ms);
+    else
+        r = wave_sweeps<L, 0>(Gw, Vw, m, n, N, tbl, ms);
+    wave_finish<L>(b, id, m, n, G, V, Gw, Vw, r, sig, perm);
+}
+
+// Problems at positions [queue[4], count) of the work order.
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4)))
+void batched_wave_kernel(BatchArgs b) {
+    extern __shared__ double lds_g[];  // G, then V
+    __shared__ double sig[kWaveMaxN];
+    __shared__ int perm[kWaveMaxN];
+    const int lane = threadIdx.x;
+    // One of kWaveQueues counters, since one would hand out a problem only every
+    // 11 ns; the next problem's index is fetched while this one is worked on.
+    // (A grid smaller than kWaveQueues has a wave for every problem.)
+    int *const queue = b.queue + kWaveQueueAt + kWaveQueueGap * (blockIdx.x % kWaveQueues);
+    int next = lane == 0 ? atomicAdd(queue, kWaveQueues) : 0;
+    for (;;) {
+        const int item = __builtin_amdgcn_readfirstlane(next);
+        if (item >= b.count) break;  // every wave leaves once the queue is drained
+        next = lane == 0 ? atomicAdd(queue, kWaveQueues) : 0;
+        const int id = b.order[item];
+        const int m = b.m[id], n = b.n[id];
+        const int N = b.tbl_order[n];
+        if (N > 16)
+            wave_problem<4>(b, id, m, n, N, lds_g, sig, perm);
+        else if (N > 8)
+            wave_problem<8>(b, id, m, n, N, lds_g, sig, perm);
+        else if (N > 4)
+            wave_problem<16>(b, id, m, n, N, lds_g, sig, perm);
+        else
+            wave_problem<32>(b, id, m, n, N, lds_g, sig, perm);
+    }
+}
+
 // Problems at positions [0, queue[2]) of the work order (the largest, n >=
 // blk_min_n): the blocked method, G and V in their global buffers.  A
 // kernel of its own so that its registers are allocated apart from the
@@ -488,10 +716,32 @@ void batched_blocked_kernel(BatchArgs b) {
     }
 }
 
-// Work order: problem indices by non-increasing n (counting sort).
-__global__ void batch_count_kernel(const int32_t *n, int64_t count, int *hist) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < count) atomicAdd(&hist[n[i]], 1);
+// Work order: problem indices by non-increasing n (counting sort), those for
+// the wave kernel after all others.  Buckets: n, or kBatchMaxN + 1 + n for the
+// wave kernel's.
+__device__ __forceinline__ bool wave_fits(int m, int n, int wave_lds, bool v) {
+    return n <= kWaveMaxN && (int64_t)m * n + (v ? n * n : 0) <= wave_lds;
+}
+
+__device__ __forceinline__ int batch_bucket(const BatchArgs &b, int64_t i) {
+    const int n = b.n[i];
+    return wave_fits(b.m[i], n, b.wave_lds, b.V != nullptr) ? kBatchMaxN + 1 + n : n;
+}
+
+// Both passes count in LDS first and go to the global buckets once per
+// workgroup and bucket: atomics on one address take 11 ns each (20000 equal
+// problems: 229 us per pass, now 5).
+constexpr int kSortThreads = 256, kSortItems = 1024;  // per workgroup
+
+__global__ __launch_bounds__(kSortThreads) void batch_count_kernel(BatchArgs b, int *hist) {
+    __shared__ int h[kBatchBuckets];
+    for (int v = threadIdx.x; v < kBatchBuckets; v += kSortThreads) h[v] = 0;
+    __syncthreads();
+    const int64_t i0 = (int64_t)blockIdx.x * kSortItems, i1 = min(b.count, i0 + kSortItems);
+    for (int64_t i = i0 + threadIdx.x; i < i1; i += kSortThreads) atomicAdd(&h[batch_bucket(b, i)], 1);
+    __syncthreads();
+    for (int v = threadIdx.x; v < kBatchBuckets; v += kSortThreads)
+        if (h[v]) atomicAdd(&hist[v], h[v]);
 }
 
 __global__ void batch_scan_kernel(int *hist, int max_n, int blk_min_n, int *queue) {
@@ -508,12 +758,40 @@ __global__ void batch_scan_kernel(int *hist, int max_n, int blk_min_n, int *queu
         queue[0] = 0;     // next blocked problem
         queue[1] = nblk;  // next pointwise problem
         queue[2] = nblk;  // number of blocked problems
+        queue[4] = pos;   // number of problems before those
+        for (int v = kBatchBuckets - 1; v > kBatchMaxN; --v) {
+            const int c = hist[v];
+            hist[v] = pos;
+            pos += c;
+        }
+        // the wave kernel's counters: queue c hands out every kWaveQueues-th one
+        for (int c = 0; c < kWaveQueues; ++c) queue[kWaveQueueAt + kWaveQueueGap * c] = queue[4] + c;
     }
 }
 
-__global__ void batch_place_kernel(const int32_t *n, int64_t count, int *hist, int32_t *order) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < count) order[atomicAdd(&hist[n[i]], 1)] = (int32_t)i;
+__global__ __launch_bounds__(kSortThreads) void batch_place_kernel(BatchArgs b, int *hist,
+                                                                   int32_t *order) {
+    __shared__ int h[kBatchBuckets];
+    for (int v = threadIdx.x; v < kBatchBuckets; v += kSortThreads) h[v] = 0;
+    __syncthreads();
+    constexpr int PER = kSortItems / kSortThreads;
+    const int64_t i0 = (int64_t)blockIdx.x * kSortItems;
+    int bucket[PER], rank[PER];
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+        const int64_t i = i0 + threadIdx.x + u * kSortThreads;
+        bucket[u] = i < b.count ? batch_bucket(b, i) : -1;
+        rank[u] = bucket[u] >= 0 ? atomicAdd(&h[bucket[u]], 1) : 0;
+    }
+    __syncthreads();
+    // h[v]: where this workgroup's problems of bucket v start
+    for (int v = threadIdx.x; v < kBatchBuckets; v += kSortThreads)
+        if (h[v]) h[v] = atomicAdd(&hist[v], h[v]);
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < PER; ++u)
+        if (bucket[u] >= 0)
+            order[h[bucket[u]] + rank[u]] = (int32_t)(i0 + threadIdx.x + u * kSortThreads);
 }
 
 __global__ void batch_zero_kernel(int *p, int count) {
@@ -535,22 +813,24 @@ hipError_t batched_set_lds(int bytes) {
     return e;
 }
 
-hipError_t launch_batched(const BatchArgs &b, int grid, int bgrid, int max_n, int *hist,
+hipError_t launch_batched(const BatchArgs &b, int grid, int bgrid, int wgrid, int max_n, int *hist,
                           int32_t *order, hipStream_t s) {
-    hipLaunchKernelGGL(batch_zero_kernel, dim3(1), dim3(256), 0, s, hist, max_n + 1);
-    const unsigned blocks = (unsigned)((b.count + 255) / 256);
-    hipLaunchKernelGGL(batch_count_kernel, dim3(blocks), dim3(256), 0, s, b.n, b.count, hist);
+    hipLaunchKernelGGL(batch_zero_kernel, dim3(1), dim3(256), 0, s, hist, kBatchBuckets);
+    const unsigned blocks = (unsigned)((b.count + kSortItems - 1) / kSortItems);
+    hipLaunchKernelGGL(batch_count_kernel, dim3(blocks), dim3(kSortThreads), 0, s, b, hist);
     hipLaunchKernelGGL(batch_scan_kernel, dim3(1), dim3(64), 0, s, hist, max_n, b.blk_min_n,
                        b.queue);
-    hipLaunchKernelGGL(batch_place_kernel, dim3(blocks), dim3(256), 0, s, b.n, b.count, hist,
-                       order);
+    hipLaunchKernelGGL(batch_place_kernel, dim3(blocks), dim3(kSortThreads), 0, s, b, hist, order);
     if (b.blk_min_n > 0 && max_n >= b.blk_min_n)
         hipLaunchKernelGGL(batched_blocked_kernel, dim3(bgrid), dim3(kBlkThreads),
                            (unsigned)(kBlkLdsDoubles * sizeof(double)), s, b);
+    if (b.wave_lds > 0)
+        hipLaunchKernelGGL(batched_wave_kernel, dim3(wgrid), dim3(64),
+                           (unsigned)(b.wave_lds * sizeof(double)), s, b);
     if (b.ddrjac)
         hipLaunchKernelGGL(batched_kernel<true>, dim3(grid), dim3(kBatchThreads),
                            (unsigned)(b.lds_doubles * sizeof(double)), s, b);
-    else
+    else if (!b.all_wave)
         hipLaunchKernelGGL(batched_kernel<false>, dim3(grid), dim3(kBatchThreads),
                            (unsigned)(b.lds_doubles * sizeof(double)), s, b);
     return hipGetLastError();

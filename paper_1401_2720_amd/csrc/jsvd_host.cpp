@@ -1082,21 +1082,24 @@ int ensure_batch_tables(jsvd_handle_s *h) {
 // Launch geometry and workspace carve-up of a batched call: the work order
 // histogram, the order itself and the queue counters.
 struct BatchPlan {
-    int grid, bgrid;
+    int grid, bgrid, wgrid;
     size_t off_hist, off_order, off_queue, total;
 };
 
-constexpr size_t batch_off_order() { return ((kBatchMaxN + 1) * sizeof(int) + 255) / 256 * 256; }
+constexpr size_t batch_off_order() { return (kBatchBuckets * sizeof(int) + 255) / 256 * 256; }
 constexpr size_t batch_off_queue(int64_t batch) {
     return batch_off_order() + ((size_t)batch * sizeof(int32_t) + 255) / 256 * 256;
 }
-constexpr size_t batch_ws_bytes(int64_t batch) { return batch_off_queue(batch) + 256; }
+constexpr size_t batch_ws_bytes(int64_t batch) {
+    return batch_off_queue(batch) + kBatchQueueInts * sizeof(int);
+}
 
 BatchPlan batch_plan(const jsvd_handle_s *h, int64_t batch) {
     BatchPlan p;
     const int cus = std::max(1, h->cu_count);
     p.grid = (int)std::min<int64_t>(std::max<int64_t>(batch, 1), cus);
     p.bgrid = (int)std::min<int64_t>(std::max<int64_t>(batch, 1), 2 * (int64_t)cus);
+    p.wgrid = (int)std::min<int64_t>(std::max<int64_t>(batch, 1), 16 * (int64_t)cus);
     p.off_hist = 0;
     p.off_order = batch_off_order();
     p.off_queue = batch_off_queue(batch);
@@ -1438,7 +1441,8 @@ int check_batched_args(jsvd_handle_t h, int64_t batch, int32_t max_m, int32_t ma
 // Enqueue the batched solve with its workspace at ws (batch_plan(h,
 // batch).total bytes): the work-order kernels, then the two persistent
 // launches.  Allocates nothing.
-int launch_batched_solve(jsvd_handle_s *h, int64_t batch, int32_t max_n, const int32_t *m,
+int launch_batched_solve(jsvd_handle_s *h, int64_t batch, int32_t max_m, int32_t max_n,
+                         const int32_t *m,
                          const int32_t *n, const int64_t *a_off, const int64_t *s_off,
                          const int64_t *v_off, double *A, double *S, double *V,
                          const jsvd_opts &o, int32_t *status, int32_t *sweeps, char *ws) {
@@ -1477,8 +1481,23 @@ int launch_batched_solve(jsvd_handle_s *h, int64_t batch, int32_t max_n, const i
     // opts.scaled = 2: DDRJAC pairs and DRDSSQ norms, every problem pointwise
     b.ddrjac = o.scaled == 2 ? 1 : 0;
     if (b.ddrjac) b.blk_min_n = 0;
+    // one wave per small problem, with LDS for the largest that the bounds
+    // allow, up to kWaveMaxLds (smaller bounds, more waves on a CU).  Where
+    // every n <= kWaveMaxN fits it takes the pointwise kernel's place (20000
+    // problems of 20 x 12: 5.9 -> 1.16 ms); where some do not, both run, one
+    // after the other, and the second launch's tail (0.8 ms: 4000 ragged problems
+    // 13.6 -> 14.4 ms) is worth it only in a large batch.
+    {
+        const int64_t wn = std::min<int64_t>(max_n, kWaveMaxN);
+        const int64_t want = (int64_t)max_m * wn + (o.want_v ? wn * wn : 0);
+        const bool fits = want <= kWaveMaxLds;
+        b.wave_lds = !b.ddrjac && (fits || batch >= kWaveMinBatch)
+                         ? (int)std::min<int64_t>(want, kWaveMaxLds) : 0;
+        b.all_wave = b.wave_lds && fits &&
+                     (max_n <= kWaveMaxN || (b.blk_min_n > 0 && b.blk_min_n <= kWaveMaxN + 1));
+    }
     for (int lg = 0; lg < 32; ++lg) b.t_hi[lg] = b.ddrjac ? rdssq_t_hi(lg) : 0.0;
-    HIP_TRY(launch_batched(b, bp.grid, bp.bgrid, max_n, reinterpret_cast<int *>(ws + bp.off_hist),
+    HIP_TRY(launch_batched(b, bp.grid, bp.bgrid, bp.wgrid, max_n, reinterpret_cast<int *>(ws + bp.off_hist),
                            reinterpret_cast<int32_t *>(ws + bp.off_order), h->stream));
     return JSVD_OK;
 }
@@ -1506,7 +1525,7 @@ int jsvd_gesvd_batched(jsvd_handle_t h, int64_t batch, int32_t max_m, int32_t ma
     int rc = ensure_batch_workspace(h, batch_plan(h, batch).total, capturing);
     if (rc) return rc;
     if (capturing) h->bws_captured = true;
-    return launch_batched_solve(h, batch, max_n, m, n, a_off, s_off, v_off, A, S, V, o, status,
+    return launch_batched_solve(h, batch, max_m, max_n, m, n, a_off, s_off, v_off, A, S, V, o, status,
                                 sweeps, static_cast<char *>(h->bws));
 }
 
@@ -1524,7 +1543,7 @@ int jsvd_gesvd_batched_noalloc(jsvd_handle_t h, int64_t batch, int32_t max_m, in
     if (!h->noalloc_scratch || !h->batch_tables) return JSVD_HIP_ERROR;
     if (batch_plan(h, batch).total > kNoAllocScratchBytes) return -2;
     if (hipSetDevice(h->device) != hipSuccess) return JSVD_HIP_ERROR;
-    return launch_batched_solve(h, batch, max_n, m, n, a_off, s_off, v_off, A, S, V, o, status,
+    return launch_batched_solve(h, batch, max_m, max_n, m, n, a_off, s_off, v_off, A, S, V, o, status,
                                 sweeps, static_cast<char *>(h->noalloc_scratch));
 }
 

@@ -122,6 +122,13 @@ hipError_t launch_fused(int nquads, const StepArgs &a, hipStream_t s);
 constexpr int kBatchMaxN = 256;  // largest n of a problem in the batched path
 constexpr int kBatchBlockMinN = 65;     // built-in: batched problems with n >= this are blocked
 constexpr int kBatchBlockLds = 9512;   // doubles of LDS the blocked method needs
+constexpr int kWaveMaxN = 32;           // largest n of a problem that one wave solves
+constexpr int kWaveMaxLds = 3072;       // doubles of LDS of such a wave, at most (64 x 32, and V)
+constexpr int kWaveMinBatch = 8192;     // batches of this size use the wave kernel beside the
+                                        // pointwise one
+constexpr int kWaveQueues = 16, kWaveQueueAt = 64, kWaveQueueGap = 32;  // its counters (ints)
+constexpr int kBatchQueueInts = kWaveQueueAt + kWaveQueues * kWaveQueueGap;
+constexpr int kBatchBuckets = kBatchMaxN + 1 + kWaveMaxN + 1;  // of the work order's sort
 constexpr int kBatchInnerOrder = 32;   // 2w of the blocked method's inner sweeps
 
 struct BatchArgs {
@@ -130,7 +137,9 @@ struct BatchArgs {
     const int64_t *a_off, *s_off, *v_off;       // device, element offsets
     double *A, *S, *V;                          // V may be null
     const int32_t *order;                       // device, work order (by non-increasing n)
-    int *queue;                                 // device: next blocked, next pointwise, blocked count
+    int *queue;                                 // device: next blocked, next pointwise, blocked count,
+                                                // (unused), problems before the wave kernel's first;
+                                                // from kWaveQueueAt its counters
     const int *tbl_order;                       // device [kBatchMaxN + 1]: strategy order for n
     const int64_t *tbl_off;                     // device: offset of the order-N table at [N/2]
     const unsigned char *tbls;                  // device: concatenated zero-based pair tables
@@ -140,6 +149,8 @@ struct BatchArgs {
     int64_t lds_doubles;                        // problems with m n <= this work in LDS
     int g_groups;                               // half waves rotating G when V is wanted (of 32)
     int blk_min_n;                              // problems with n >= this are blocked (0: none)
+    int wave_lds;                               // doubles of LDS per problem of the wave kernel (0: none)
+    int all_wave;                               // every problem goes to the blocked or the wave kernel
     int ddrjac;                                 // 1: DDRJAC pairs and DRDSSQ norms (no blocked problems)
     double t_hi[32];                            // DRDSSQ upper bound by ceil(lg m)
 };
@@ -152,8 +163,8 @@ hipError_t batched_set_lds(int bytes);
 double rdssq_t_hi(int lg);
 
 // grid: workgroups of the pointwise kernel; bgrid: of the blocked kernel
-// (two fit on a CU).
-hipError_t launch_batched(const BatchArgs &b, int grid, int bgrid, int max_n, int *hist,
+// (two fit on a CU); wgrid: of the wave kernel.
+hipError_t launch_batched(const BatchArgs &b, int grid, int bgrid, int wgrid, int max_n, int *hist,
                           int32_t *order, hipStream_t s);
 
 // ------------------------------------------------------------ SVD adjoint

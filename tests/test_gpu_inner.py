@@ -118,3 +118,30 @@ def test_batched_blocked_edges(n):
     for i, A in enumerate(mats):
         U, S, V = b.results(i)
         _check(A, U, S, V, np.linalg.svd(A, compute_uv=False))
+
+
+# the batched path's one-wave problems: every lane-group width (n up to 4, 8,
+# 16, 32), rows in registers or not, and the first sizes that do not fit a wave
+@pytest.mark.parametrize("want_v", [True, False])
+def test_batched_wave_edges(want_v):
+    torch, jsvd = _jsvd()
+    g = np.random.default_rng(5)
+    sizes = [(1, 1), (7, 1), (3, 2), (70, 2), (4, 4), (33, 5), (8, 8), (9, 9), (17, 12), (16, 16),
+             (65, 16), (17, 17), (33, 25), (32, 32), (64, 32), (65, 32), (90, 24), (300, 7),
+             (300, 20), (40, 33)]
+    mats = [g.standard_normal(s) for s in sizes]
+    mats.append(g.standard_normal((30, 18)) * 10.0 ** -np.linspace(0, 12, 18))
+    mats.append(np.zeros((12, 6)))
+    mats.append(np.repeat(g.standard_normal((20, 1)), 5, axis=1))
+    b = jsvd.Batch(mats, want_v=want_v)
+    jsvd.gesvd_batched(b)
+    torch.cuda.synchronize()
+    assert int(b.status.abs().sum()) == 0
+    for i, A in enumerate(mats):
+        U, S, V = b.results(i)
+        ref = oracle.gesvj(A)["S"]
+        if want_v:
+            _check(A, U, S, V, ref)
+        assert np.all(np.abs(S - ref) <= 1e-12 * ref + 1e-13 * ref[0])
+        U = U[:, S > 1e-10 * S[0]]
+        assert np.max(np.abs(U.T @ U - np.eye(U.shape[1])), initial=0.0) <= 1e-13 * 40
