@@ -19,84 +19,152 @@ namespace jsvd {
 
 namespace {
 
+// two doubles loaded as one 16-byte access (8-byte alignment suffices)
+typedef double d2u __attribute__((ext_vector_type(2), aligned(8)));
+
 // C = alpha op(A) op(B) + beta C [+ E diag(d)] for a batch of column-major
 // matrices, or (split-K) one product whose K range is cut into slices, slice
 // b summed into the b-th C of the batch.
-// op(A) is M x K, op(B) is K x N.  Workgroup tile 64 x 64 (four waves of
-// 32 x 32, each 2 x 2 MFMA tiles of 16 x 16), K step 16 staged in LDS.
-// MFMA lane layout: lane l supplies A[l%16][l/16] and B[l/16][l%16]; the
-// result holds D[l/16 + 4v][l%16] in element v.
-__global__ __launch_bounds__(256) void gemm_f64_kernel(GemmArgs g) {
-    __shared__ double As[16][64 + 1];  // As[k][i] = op(A)[i0 + i][k0 + k]
-    __shared__ double Bs[16][64 + 1];  // Bs[k][j] = op(B)[k0 + k][j0 + j]
+// op(A) is M x K, op(B) is K x N.  Workgroup tile 32 WT x 32 WT (4 WT waves
+// of WT x 1 MFMA tiles of 16 x 16: two waves per SIMD at WT = 2 cover each
+// other's LDS reads), K steps of 32 through two LDS buffers.  Loads are issued
+// two steps ahead, into registers, and stored to the buffer one step later (a
+// step is 2048 cycles of MFMA at WT = 2, less than a load's latency).  MFMA lane layout: lane l
+// supplies A[l%16][l/16] and B[l/16][l%16], element v of the result is
+// D[l/16 + 4v][l%16]; op(B)^T takes the A operand's place, so that the lanes
+// of a result are consecutive rows of C.  Bound by the MFMAs and the wait for
+// the slowest wave at each step's barrier: 1024^3 takes 57 us (38 TFLOP/s), with
+// 16-column steps that each waited for their loads 240 us.
+constexpr int kGemmK = 32;
+template <int T>
+constexpr int kGemmThreads = T == 64 ? 512 : 256;
+
+// A 32 x T slice of an operand, element (k, i), i < T: at src[k + i ld] (ALONG_K)
+// or src[i + k ld]; nk and ni of its rows and columns exist.  Thread t holds
+// its elements as pairs of neighbours in memory.
+template <int T, bool ALONG_K>
+__device__ __forceinline__ void gemm_load(const double *src, int64_t ld, int nk, int ni,
+                                          double (&x)[2 * (16 * T / kGemmThreads<T>)]) {
+    const int t = threadIdx.x;
+#pragma unroll
+    for (int u = 0; u < 16 * T / kGemmThreads<T>; ++u) {
+        const int e = t + kGemmThreads<T> * u;  // pair index
+        const int k = ALONG_K ? 2 * (e % 16) : e / (T / 2);
+        const int i = ALONG_K ? e / 16 : 2 * (e % (T / 2));
+        const double *p = ALONG_K ? src + k + (int64_t)i * ld : src + i + (int64_t)k * ld;
+        const bool in = k < nk && i < ni;
+        const bool both = in && (ALONG_K ? k + 1 < nk : i + 1 < ni);
+        if (both) {
+            const d2u v = *reinterpret_cast<const d2u *>(p);
+            x[2 * u] = v.x;
+            x[2 * u + 1] = v.y;
+        } else {
+            x[2 * u] = in ? *p : 0.0;
+            x[2 * u + 1] = 0.0;
+        }
+    }
+}
+
+template <int T, bool ALONG_K>
+__device__ __forceinline__ void gemm_stage(double *s,
+                                           const double (&x)[2 * (16 * T / kGemmThreads<T>)]) {
+    constexpr int LD = T + 2;
+    const int t = threadIdx.x;
+#pragma unroll
+    for (int u = 0; u < 16 * T / kGemmThreads<T>; ++u) {
+        const int e = t + kGemmThreads<T> * u;
+        if (ALONG_K) {
+            const int k = 2 * (e % 16), i = e / 16;
+            s[k * LD + i] = x[2 * u];
+            s[(k + 1) * LD + i] = x[2 * u + 1];
+        } else {
+            const int k = e / (T / 2), i = 2 * (e % (T / 2));
+            *reinterpret_cast<double2 *>(s + k * LD + i) = make_double2(x[2 * u], x[2 * u + 1]);
+        }
+    }
+}
+
+template <int WT, bool TA, bool TB>
+__global__ __launch_bounds__(kGemmThreads<32 * WT>) void gemm_f64_kernel(GemmArgs g) {
+    constexpr int T = 32 * WT, LD = T + 2, KT = kGemmK;
+    constexpr int WY = 1;  // 16-column tiles per wave (WT 16-row ones)
+    __shared__ __align__(16) double As[2][KT * LD];  // As[k][i] = op(A)[i0 + i][k0 + k]
+    __shared__ __align__(16) double Bs[2][KT * LD];  // Bs[k][j] = op(B)[k0 + k][j0 + j]
     const int b = blockIdx.z;
-    const int i0 = blockIdx.x * 64, j0 = blockIdx.y * 64;
-    const double *A = g.A + (g.ksplit ? 0 : (size_t)b * g.sa);
-    const double *B = g.B + (g.ksplit ? 0 : (size_t)b * g.sb);
+    // Workgroups go to the 8 XCDs round robin: where the grid of tiles divides
+    // into 4 x 2 blocks, each XCD takes one of them, so that its L2 sees a
+    // quarter of A and half of B.
+    int bx = blockIdx.x, by = blockIdx.y;
+    if (gridDim.x % 4 == 0 && gridDim.y % 2 == 0) {
+        const int lin = bx + gridDim.x * by, xcd = lin % 8, i = lin / 8, w = gridDim.x / 4;
+        bx = (xcd % 4) * w + i % w;
+        by = (xcd / 4) * (gridDim.y / 2) + i / w;
+    }
+    const int i0 = bx * T, j0 = by * T;
+    const double *A = g.A + (g.ksplit ? 0 : (size_t)b * g.sa) + (TA ? (size_t)i0 * g.lda : i0);
+    const double *B = g.B + (g.ksplit ? 0 : (size_t)b * g.sb) + (TB ? j0 : (size_t)j0 * g.ldb);
     double *C = g.C + (size_t)b * g.sc;
     // K range of this product (split-K: one slice per batch index)
     const int kbeg = g.ksplit ? (int)min((int64_t)g.K, (int64_t)b * g.ksplit) : 0;
     const int kend = g.ksplit ? (int)min((int64_t)g.K, (int64_t)(b + 1) * g.ksplit) : g.K;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wi = (wave & 1) * 32, wj = (wave >> 1) * 32;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int wi = (wave & 1) * 16 * WT, wj = (wave >> 1) * 16;
     const int l16 = lane & 15, lg = lane >> 4;
-    d4 acc[2][2];
-    for (int x = 0; x < 2; ++x)
-        for (int y = 0; y < 2; ++y) acc[x][y] = d4{0.0, 0.0, 0.0, 0.0};
+    const int ni = g.M - i0, nj = g.N - j0;
+    d4 acc[WT][WY];
+#pragma unroll
+    for (int x = 0; x < WT; ++x)
+#pragma unroll
+        for (int y = 0; y < WY; ++y) acc[x][y] = d4{0.0, 0.0, 0.0, 0.0};
 
-    for (int k0 = kbeg; k0 < kend; k0 += 16) {
-        // stage op(A)[i0 .. i0+63][k0 .. k0+15] and op(B)[k0 .. k0+15][j0 .. j0+63]
-        for (int e = tid; e < 64 * 16; e += 256) {
-            int i, k;
-            if (g.ta) {  // op(A) = A^T: element (i, k) at A[k + i * lda]; read along k
-                k = e % 16;
-                i = e / 16;
-            } else {     // element (i, k) at A[i + k * lda]; read along i
-                i = e % 64;
-                k = e / 64;
-            }
-            const int gi = i0 + i, gk = k0 + k;
-            double v = 0.0;
-            if (gi < g.M && gk < kend) v = g.ta ? A[gk + (size_t)gi * g.lda] : A[gi + (size_t)gk * g.lda];
-            As[k][i] = v;
+    constexpr int NX = 2 * (16 * T / kGemmThreads<T>);
+    auto load = [&](int k0, double (&xa)[NX], double (&xb)[NX]) __attribute__((always_inline)) {
+        gemm_load<T, TA>(A + (TA ? k0 : (size_t)k0 * g.lda), g.lda, kend - k0, ni, xa);
+        gemm_load<T, !TB>(B + (TB ? (size_t)k0 * g.ldb : k0), g.ldb, kend - k0, nj, xb);
+    };
+    auto stage = [&](int buf, const double (&xa)[NX], const double (&xb)[NX]) __attribute__((always_inline)) {
+        gemm_stage<T, TA>(As[buf], xa);
+        gemm_stage<T, !TB>(Bs[buf], xb);
+    };
+    // one K step: (xa, xb) hold the next step's tiles and go to the other
+    // buffer, (ya, yb) receive the one after's
+    auto step = [&](int k0, int buf, const double (&xa)[NX], const double (&xb)[NX], double (&ya)[NX],
+                    double (&yb)[NX]) __attribute__((always_inline)) {
+        if (k0 + 2 * KT < kend) load(k0 + 2 * KT, ya, yb);
+#pragma unroll
+        for (int kk = 0; kk < KT; kk += 4) {
+            double av[WT], bv[WY];
+#pragma unroll
+            for (int x = 0; x < WT; ++x) av[x] = As[buf][(kk + lg) * LD + wi + 16 * x + l16];
+#pragma unroll
+            for (int y = 0; y < WY; ++y) bv[y] = Bs[buf][(kk + lg) * LD + wj + 16 * y + l16];
+#pragma unroll
+            for (int x = 0; x < WT; ++x)
+#pragma unroll
+                for (int y = 0; y < WY; ++y) acc[x][y] = mfma16(bv[y], av[x], acc[x][y]);
         }
-        for (int e = tid; e < 16 * 64; e += 256) {
-            int k, j;
-            if (g.tb) {  // op(B) = B^T: element (k, j) at B[j + k * ldb]; read along j
-                j = e % 64;
-                k = e / 64;
-            } else {     // element (k, j) at B[k + j * ldb]; read along k
-                k = e % 16;
-                j = e / 16;
-            }
-            const int gk = k0 + k, gj = j0 + j;
-            double v = 0.0;
-            if (gk < kend && gj < g.N) v = g.tb ? B[gj + (size_t)gk * g.ldb] : B[gk + (size_t)gj * g.ldb];
-            Bs[k][j] = v;
-        }
+        if (k0 + KT < kend) stage(buf ^ 1, xa, xb);
         __syncthreads();
-#pragma unroll
-        for (int kk = 0; kk < 16; kk += 4) {
-            double av[2], bv[2];
-#pragma unroll
-            for (int x = 0; x < 2; ++x) av[x] = As[kk + lg][wi + 16 * x + l16];
-#pragma unroll
-            for (int y = 0; y < 2; ++y) bv[y] = Bs[kk + lg][wj + 16 * y + l16];
-#pragma unroll
-            for (int x = 0; x < 2; ++x)
-#pragma unroll
-                for (int y = 0; y < 2; ++y) acc[x][y] = mfma16(av[x], bv[y], acc[x][y]);
-        }
-        __syncthreads();
+    };
+    double xa[NX] = {}, xb[NX] = {}, ya[NX] = {}, yb[NX] = {};
+    if (kbeg < kend) {
+        load(kbeg, xa, xb);
+        stage(0, xa, xb);
+        if (kbeg + KT < kend) load(kbeg + KT, xa, xb);
+    }
+    __syncthreads();
+    for (int k0 = kbeg; k0 < kend; k0 += 2 * KT) {
+        step(k0, 0, xa, xb, ya, yb);
+        if (k0 + KT < kend) step(k0 + KT, 1, ya, yb, xa, xb);
     }
 #pragma unroll
-    for (int x = 0; x < 2; ++x)
+    for (int x = 0; x < WT; ++x)
 #pragma unroll
-        for (int y = 0; y < 2; ++y)
+        for (int y = 0; y < WY; ++y)
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
-                const int gi = i0 + wi + 16 * x + lg + 4 * v;
-                const int gj = j0 + wj + 16 * y + l16;
+                const int gi = i0 + wi + 16 * x + l16;
+                const int gj = j0 + wj + 16 * y + lg + 4 * v;
                 if (gi < g.M && gj < g.N) {
                     double r = g.alpha == 1.0 ? acc[x][y][v] : g.alpha * acc[x][y][v];
                     if (g.beta != 0.0) r = fma(g.beta, C[gi + (size_t)gj * g.ldc], r);
@@ -106,15 +174,27 @@ __global__ __launch_bounds__(256) void gemm_f64_kernel(GemmArgs g) {
             }
 }
 
+template <int WT>
+void gemm_f64(const GemmArgs &g, hipStream_t s) {
+    constexpr int T = 32 * WT;
+    const dim3 grid((unsigned)((g.M + T - 1) / T), (unsigned)((g.N + T - 1) / T), (unsigned)g.batch);
+    const dim3 blk(kGemmThreads<T>);
+    if (g.ta && g.tb)
+        hipLaunchKernelGGL((gemm_f64_kernel<WT, true, true>), grid, blk, 0, s, g);
+    else if (g.ta)
+        hipLaunchKernelGGL((gemm_f64_kernel<WT, true, false>), grid, blk, 0, s, g);
+    else if (g.tb)
+        hipLaunchKernelGGL((gemm_f64_kernel<WT, false, true>), grid, blk, 0, s, g);
+    else
+        hipLaunchKernelGGL((gemm_f64_kernel<WT, false, false>), grid, blk, 0, s, g);
+}
+
 // out_b (M x N, ld M) = A[rows of slice b]^T B[rows of slice b], slices of
 // ksplit rows; M <= 16 MT.  Grid (column blocks of 64, slices), 256
 // threads: the four waves take 8-row steps of the slice (each lane 2
 // consecutive rows of one column of A and of B: the same rows are the
 // contraction index of both MFMA operands), and their accumulators are
 // summed in a fixed order at the end.
-// two doubles loaded as one 16-byte access (8-byte alignment suffices)
-typedef double d2u __attribute__((ext_vector_type(2), aligned(8)));
-
 template <int MT>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void gemm_tn_rows_kernel(const double *A, int64_t lda,
                                                            const double *B, int64_t ldb, int M,
@@ -283,8 +363,15 @@ hipError_t launch_gemm(const GemmArgs &g, hipStream_t s) {
                            g.ldc, g.M, g.N, g.K, g.alpha, g.beta);
         return hipGetLastError();
     }
-    dim3 grid((unsigned)((g.M + 63) / 64), (unsigned)((g.N + 63) / 64), (unsigned)g.batch);
-    hipLaunchKernelGGL(gemm_f64_kernel, grid, dim3(256), 0, s, g);
+    // 64 x 64 tiles where they give a workgroup per CU (256), 32 x 32 below
+    // (more of the chip, each operand read twice as often).  The adjoint's five
+    // products at 1024 x 1024 (256 tiles of 64): 0.27 ms with 64 x 64, 0.31 ms
+    // with 32 x 32; at 700 x 500 (88 tiles) 0.11 ms with 32 x 32.
+    const int64_t tiles = (int64_t)((g.M + 63) / 64) * ((g.N + 63) / 64) * g.batch;
+    if (tiles >= 256)
+        gemm_f64<2>(g, s);
+    else
+        gemm_f64<1>(g, s);
     return hipGetLastError();
 }
 
