@@ -47,6 +47,11 @@ struct DeviceTable {
     size_t bytes = 0;
 };
 
+struct StepGroups {
+    std::vector<int> at;  // per step (step_groups)
+    DeviceTable table;
+};
+
 }  // namespace
 
 // Pinned host words of a handle: the per-sweep counters, then single
@@ -70,6 +75,7 @@ struct jsvd_handle_s {
     std::map<std::pair<int, int>, DeviceTable> block_tables;  // (order, kind) -> int2[]
     std::map<std::pair<int, int>, DeviceTable> inner_tables;  // (bw, kind) -> uchar[]
     std::map<std::pair<int, int>, DeviceTable> quad_tables;   // (order, kind) -> int[8][]
+    std::map<std::pair<int, int>, StepGroups> step_groups;    // (order, kind)
     // batched path: strategy tables of every order up to kBatchMaxN
     void *batch_tables = nullptr;   // uchar pairs
     const unsigned char *batch_jac = nullptr;  // position_tables' of order 32, in batch_tables
@@ -189,6 +195,34 @@ int get_quad_table(jsvd_handle_s *h, int order, int kind, const int **out) {
         it = h->quad_tables.emplace(key, d).first;
     }
     *out = static_cast<const int *>(it->second.ptr);
+    return JSVD_OK;
+}
+
+// The steps of a block table two by two (step_groups): at, per step, and the
+// quads on the device (null when no two steps go together).
+int get_step_groups(jsvd_handle_s *h, int order, int kind, const std::vector<int> **at,
+                    const int **out) {
+    auto key = std::make_pair(order, kind);
+    auto it = h->step_groups.find(key);
+    if (it == h->step_groups.end()) {
+        Table t;
+        if (!make_table(order, kind, t)) return JSVD_HIP_ERROR;
+        std::vector<int> flat;
+        StepGroups g;
+        step_groups(t, g.at, flat);
+        if (!flat.empty()) {
+            g.table.bytes = flat.size() * sizeof(int);
+            HIP_TRY(hipMalloc(&g.table.ptr, g.table.bytes));
+            if (hipMemcpy(g.table.ptr, flat.data(), g.table.bytes, hipMemcpyHostToDevice) !=
+                hipSuccess) {
+                (void)hipFree(g.table.ptr);
+                return JSVD_HIP_ERROR;
+            }
+        }
+        it = h->step_groups.emplace(key, g).first;
+    }
+    *at = &it->second.at;
+    *out = static_cast<const int *>(it->second.table.ptr);
     return JSVD_OK;
 }
 
@@ -315,6 +349,10 @@ struct Layout {
     size_t hpart, vprime, pair_rot, counters, perm, s_tmp, tmp, perm_in, rscratch, total;
 };
 
+// Slots of V'_pq: a p-step's is read by the next p-step's launch; where two
+// p-steps' V updates are done at once, by the three after it.
+int vprime_slots(int bw) { return bw == 64 ? 4 : 2; }
+
 Layout plan(int64_t m, int64_t n, int bw, int npairs, int splits, bool hsvd) {
     Layout L;
     size_t off = 0;
@@ -324,9 +362,8 @@ Layout plan(int64_t m, int64_t n, int bw, int npairs, int splits, bool hsvd) {
         return o;
     };
     L.hpart = take((size_t)npairs * splits * bw * bw * sizeof(double));
-    // two slots: a p-step's V'_pq is read by the next p-step's launch
-    L.vprime = take((size_t)2 * npairs * bw * bw * sizeof(double));
-    L.pair_rot = take((size_t)2 * npairs * sizeof(int));
+    L.vprime = take((size_t)vprime_slots(bw) * npairs * bw * bw * sizeof(double));
+    L.pair_rot = take((size_t)vprime_slots(bw) * npairs * sizeof(int));
     L.counters = take(C_COUNT * sizeof(unsigned long long));
     L.perm = take((size_t)n * sizeof(int));
     L.s_tmp = take((size_t)n * sizeof(double));
@@ -368,6 +405,33 @@ int column_exponents(jsvd_handle_s *h, int64_t m, int64_t n, const double *A, in
         *bad = hr[0] <= hr[1] && (hr[0] < -480 || hr[1] > 480);
     }
     return JSVD_OK;
+}
+
+// Rows of V per workgroup of a launch that applies two p-steps' V updates
+// (update_quad_rows, one workgroup per CU): the chunk of half_rows with which
+// the last workgroup ends first.  Measured per workgroup: 12 us to stage the
+// four V' and get going, and 7 us for every slice of 16 rows that a SIMD takes;
+// a CU that holds a pivot pair is free after 50 us.  At n = 4096 six chunks of
+// 352 rows per quad (62 us per launch; eight of 256: 78 us), at 8192 four of
+// 1024 (194 us; sixteen of 256: 204 us, two of 2048: 280 us).
+int64_t quad_chunk_rows(int64_t half_rows, int nquads, int npairs, int cu) {
+    const int64_t early = std::max(1, cu - npairs), late = cu - early;
+    int64_t best = 256, best_t = INT64_MAX;
+    for (int64_t chunks = 1; chunks <= std::max<int64_t>(1, half_rows / 256); ++chunks) {
+        const int64_t rows = align_up((size_t)((half_rows + chunks - 1) / chunks), 16);
+        const int64_t cost = 12 + 7 * ((rows + 63) / 64), wgs = chunks * nquads;
+        int64_t t = cost;  // of the last one: a multiple of cost, or 50 and one
+        while (early * (t / cost) + late * (t > 50 ? (t - 50) / cost : 0) < wgs) {
+            const int64_t a = (t / cost + 1) * cost;
+            const int64_t b = 50 + (t < 50 ? 1 : (t - 50) / cost + 1) * cost;
+            t = late ? std::min(a, b) : a;
+        }
+        if (t < best_t) {
+            best_t = t;
+            best = rows;
+        }
+    }
+    return best;
 }
 
 // The solver shared by the SVD and the hyperbolic SVD.  A holds G with J
@@ -427,6 +491,24 @@ int solve(jsvd_handle_s *h, int64_t m, int64_t n, double *A, int64_t lda, double
     const int64_t prev_rows =
         align_up((size_t)((n + v_per_pair - 1) / v_per_pair), (size_t)16 * inner_waves);
 
+    // V's updates of two p-steps at once where the ordering takes them in
+    // quads: V is read and written once for the two, half of its rows in
+    // either of the two launches that follow them.  n = 3000: 106 ms for the
+    // SVD against 116 ms one p-step at a time, 4096: 181 against 204 ms, 8192:
+    // 1.35 against 1.52 s; at 2300 and below V's update hides behind the inner
+    // sweeps either way (68.6 ms).  The lanes' byte offsets (4 columns) stay
+    // below 2^32.
+    const std::vector<int> *group_at = nullptr;
+    const int *vquads = nullptr;
+    if (want_v && bw == 64 && w == 32 && !scaled && !qrf && n >= 2560 &&
+        ldv <= ((int64_t)1 << 26) &&
+        (rc = get_step_groups(h, order, o.strategy, &group_at, &vquads)))
+        return rc;
+    const int lag = vquads ? 2 : 1;  // launches from a p-step to its V update
+    const int nslots = vprime_slots(bw);
+    const int64_t half_rows = align_up((size_t)((n + 1) / 2), 16);
+    const int64_t quad_rows = quad_chunk_rows(half_rows, nquads, npairs, h->cu_count);
+
     Layout L = plan(m, n, bw, npairs, splits, hsvd);
     rc = ensure_workspace(h, L.total);
     if (rc) return rc;
@@ -478,6 +560,13 @@ int solve(jsvd_handle_s *h, int64_t m, int64_t n, double *A, int64_t lda, double
     a.prev_pair_rot = nullptr;
     a.prev_chunks = 0;
     a.prev_rows = (int)prev_rows;
+    a.vquads = nullptr;
+    a.prev_n = 0;
+    a.prev2_pairs = nullptr;
+    a.prev2_vprime = nullptr;
+    a.prev2_pair_rot = nullptr;
+    a.prev_row0 = 0;
+    a.prev_row1 = n;
     const int v_chunks = want_v ? (int)((n + prev_rows - 1) / prev_rows) : 0;
 
     if (want_v) HIP_TRY(launch_init_identity(V, ldv, n, st));
@@ -498,17 +587,55 @@ int solve(jsvd_handle_s *h, int64_t m, int64_t n, double *A, int64_t lda, double
         }
     }
     int64_t g = 0;  // p-steps launched in this solve
+    // the V update that goes with launch l (a p-step's index): p-step l - lag's,
+    // or one half of the rows of the two p-steps' that it belongs to
+    auto v_task = [&](StepArgs &x, int64_t l) {
+        x.prev_chunks = 0;
+        x.prev_n = 0;
+        const int64_t t = l - lag;
+        if (t < 0 || !want_v) return;
+        auto pairs_of = [&](int64_t i) { return blk + (size_t)(i % nsteps) * npairs; };
+        auto vprime_of = [&](int64_t i) {
+            return vprime0 + (size_t)(i % nslots) * npairs * bw * bw;
+        };
+        auto rot_of = [&](int64_t i) { return pair_rot0 + (size_t)(i % nslots) * npairs; };
+        const int s = (int)(t % nsteps);
+        const int at = vquads ? (*group_at)[s] : -1;
+        if (at < 0) {
+            x.vquads = nullptr;
+            x.prev_pairs = pairs_of(t);
+            x.prev_vprime = vprime_of(t);
+            x.prev_pair_rot = rot_of(t);
+            x.prev_row0 = 0;
+            x.prev_row1 = n;
+            x.prev_rows = (int)prev_rows;
+            x.prev_chunks = v_chunks;
+            x.prev_n = npairs;
+            return;
+        }
+        const bool second = s > 0 && (*group_at)[s - 1] == at;
+        const int64_t t0 = second ? t - 1 : t;
+        x.vquads = vquads + at;
+        x.prev_pairs = pairs_of(t0);
+        x.prev_vprime = vprime_of(t0);
+        x.prev_pair_rot = rot_of(t0);
+        x.prev2_pairs = pairs_of(t0 + 1);
+        x.prev2_vprime = vprime_of(t0 + 1);
+        x.prev2_pair_rot = rot_of(t0 + 1);
+        x.prev_row0 = second ? half_rows : 0;
+        x.prev_row1 = second ? n : half_rows;
+        x.prev_rows = (int)quad_rows;
+        x.prev_n = nquads;
+        x.prev_chunks = (int)((x.prev_row1 - x.prev_row0 + quad_rows - 1) / quad_rows);
+    };
     for (int sweep = 0; sweep < o.max_sweeps; ++sweep) {
         HIP_TRY(launch_reset_counters(a.counters, st));
         for (int s = 0; s < nsteps; ++s, ++g) {
-            // the previous p-step's V update rides along with this inner launch
-            a.prev_pairs = a.pairs;
-            a.prev_vprime = a.vprime;
-            a.prev_pair_rot = a.pair_rot;
-            a.prev_chunks = g > 0 ? v_chunks : 0;
+            // an earlier p-step's V update rides along with this inner launch
+            v_task(a, g);
             a.pairs = blk + (size_t)s * npairs;
-            a.vprime = vprime0 + (size_t)(g % 2) * npairs * bw * bw;
-            a.pair_rot = pair_rot0 + (size_t)(g % 2) * npairs;
+            a.vprime = vprime0 + (size_t)(g % nslots) * npairs * bw * bw;
+            a.pair_rot = pair_rot0 + (size_t)(g % nslots) * npairs;
             // events around the kernels of every timing_stride-th p-step
             const bool timed = h->timing && s % h->timing_stride == 0;
             hipEvent_t *ev = timed ? &h->events[(size_t)4 * s] : nullptr;
@@ -568,7 +695,14 @@ int solve(jsvd_handle_s *h, int64_t m, int64_t n, double *A, int64_t lda, double
     }
     inf.converged = converged ? 1 : 0;
     if (status == JSVD_OK && !converged) status = JSVD_NOT_CONVERGED;
-    if (want_v && g > 0) {  // the last p-step's V update
+    // ---- the V updates still to do
+    for (int64_t l = g; vquads && l < g + lag; ++l) {
+        StepArgs av = a;
+        v_task(av, l);
+        av.npairs = 0;
+        HIP_TRY(launch_inner(bw, av, st));
+    }
+    if (want_v && !vquads && g > 0) {  // the last p-step's
         StepArgs av = a;
         av.upd_rows = (int)upd_rows_v;
         av.upd_chunks_g = 0;
@@ -1241,6 +1375,8 @@ int jsvd_destroy(jsvd_handle_t h) {
     for (void *p : h->bws_retired) (void)hipFree(p);
     for (auto &kv : h->block_tables) (void)hipFree(kv.second.ptr);
     for (auto &kv : h->inner_tables) (void)hipFree(kv.second.ptr);
+    for (auto &kv : h->step_groups)
+        if (kv.second.table.ptr) (void)hipFree(kv.second.table.ptr);
     for (auto &kv : h->quad_tables)
         if (kv.second.ptr) (void)hipFree(kv.second.ptr);
     if (h->batch_tables) (void)hipFree(h->batch_tables);

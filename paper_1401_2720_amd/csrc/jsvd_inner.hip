@@ -567,10 +567,16 @@ __global__ __launch_bounds__(JacCfg<BW>::kThreads) void jacobi_kernel(StepArgs a
     constexpr int NP = Cfg::kPairs, NS = Cfg::kSteps, LD = Cfg::kLD;
     constexpr int EPT = BW * BW / NT;   // Gram entries summed per thread
     constexpr int HB = BW * LD * 8;     // bytes of one buffer of H
-    __shared__ double H[2][BW * LD];
-    __shared__ __align__(16) double xch[2][NP * BW];  // columns of V' on their way, by slot
-    __shared__ uint2 tbl[NS * NP];           // position_tables' entry of every step and pair
-    __shared__ __align__(8) unsigned vctl[NS * NP];  // V waves: see below
+    // H, columns of V' on their way (xch, by slot), position_tables' entry of
+    // every step and pair, and of them what the V waves take (vctl); or the
+    // four V' of two p-steps' V updates at once
+    constexpr int kH = 2 * BW * LD, kXch = 2 * NP * BW, kTbl = NS * NP;
+    constexpr int kArena = kH + kXch + kTbl + (kTbl + 1) / 2;
+    __shared__ __align__(16) double arena[BW == 64 && kArena < 4 * BW * BW ? 4 * BW * BW : kArena];
+    double(*const H)[BW * LD] = reinterpret_cast<double(*)[BW * LD]>(arena);
+    double(*const xch)[NP * BW] = reinterpret_cast<double(*)[NP * BW]>(arena + kH);
+    uint2 *const tbl = reinterpret_cast<uint2 *>(arena + kH + kXch);
+    unsigned *const vctl = reinterpret_cast<unsigned *>(arena + kH + kXch + kTbl);
     __shared__ double diag[BW];              // h_cc by position
     __shared__ double2 prm[2][NP];           // published rotations: tan, cos (swapped: -cos)
     __shared__ double mtn[2][HYP ? NP : 1];  // -t tan (hyperbolic pairs: + tan)
@@ -579,16 +585,25 @@ __global__ __launch_bounds__(JacCfg<BW>::kThreads) void jacobi_kernel(StepArgs a
     __shared__ int rots;                     // rotations of the inner sweep
 
     if (blockIdx.x >= a.npairs) {
-        // V <- V V'_pq of the previous p-step, as in inner_kernel
-        __builtin_amdgcn_s_sleep(127);
-        __builtin_amdgcn_s_sleep(127);
+        // V <- V V'_pq of an earlier p-step, as in inner_kernel
         const int idx = blockIdx.x - a.npairs;
         const int vpair = idx / a.prev_chunks, chunk = idx % a.prev_chunks;
+        if constexpr (BW == 64) {
+            if (a.vquads) {
+                const int64_t q0 = a.prev_row0 + (int64_t)chunk * a.prev_rows;
+                update_quad_rows<NWAVES>(a.V, a.ldv, q0,
+                                         min(a.prev_row1, q0 + (int64_t)a.prev_rows),
+                                         a.vquads + 8 * vpair, a, arena, &flags);
+                return;
+            }
+        }
+        __builtin_amdgcn_s_sleep(127);
+        __builtin_amdgcn_s_sleep(127);
         if (a.prev_pair_rot[vpair] == 0) return;
         const int64_t r0 = (int64_t)chunk * a.prev_rows;
         const int64_t r1 = min(a.n, r0 + (int64_t)a.prev_rows);
         update_rows<BW, NWAVES, 1, true>(a.V, a.ldv, r0, r1, a.prev_pairs[vpair], a.w, a.n,
-                                a.prev_vprime + (size_t)vpair * BW * BW, &H[0][0]);
+                                a.prev_vprime + (size_t)vpair * BW * BW, arena);
         return;
     }
     const int pair = blockIdx.x;
@@ -1202,11 +1217,11 @@ __global__ __launch_bounds__(kW128Threads) void inner128_kernel(StepArgs a) {
 
 hipError_t launch_inner(int bw, const StepArgs &a, hipStream_t s) {
     if (bw == 128) {
-        hipLaunchKernelGGL(inner128_kernel, dim3(a.npairs * (1 + a.prev_chunks)),
+        hipLaunchKernelGGL(inner128_kernel, dim3(a.npairs + a.prev_n * a.prev_chunks),
                            dim3(kW128Threads), 0, s, a);
         return hipGetLastError();
     }
-    const dim3 grid(a.npairs * (1 + a.prev_chunks));
+    const dim3 grid(a.npairs + a.prev_n * a.prev_chunks);
     const bool hyp = a.n_plus < a.n;
     if (!a.colexp && !a.qrf) {
         // unscaled, by the Gram matrix: two-sided rotations, 1.7 to 1.8 times

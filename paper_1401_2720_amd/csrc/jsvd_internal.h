@@ -41,6 +41,12 @@ void position_tables(const Table &t, std::vector<unsigned char> &out);
 // the blocks of ia and ib that pair jx holds).  False when some step has no
 // such structure.
 bool make_quads(const Table &t, std::vector<int> &out);
+// make_quads for one step and the next one (appended to out)
+bool step_quads(const Step &cur, const Step &nxt, std::vector<int> &out);
+// The steps taken two by two where step_quads allows it: at[s] is the offset
+// in out of the quads of steps s and s + 1 (and at[s + 1] the same), -1 for a
+// step that stays single.
+void step_groups(const Table &t, std::vector<int> &at, std::vector<int> &out);
 
 // ------------------------------------------------------------------ counters
 // Per-sweep device counters (unsigned 64-bit), reset at the start of a sweep.
@@ -84,7 +90,17 @@ struct StepArgs {
     const double *prev_vprime;
     const int *prev_pair_rot;
     int prev_chunks;
+    int prev_n;         // pivot pairs (or quads) of that update
     int prev_rows;      // rows of V per such workgroup
+    // two p-steps' V updates at once on half the rows (jacobi_kernel<64>):
+    // the quads of the two steps (null: prev_* is one step's), the second
+    // step's pairs, V' and rotation counts, and the rows of V.  prev_pairs
+    // and the like are the first step's, prev_chunks is per quad.
+    const int *vquads;
+    const int2 *prev2_pairs;
+    const double *prev2_vprime;
+    const int *prev2_pair_rot;
+    int64_t prev_row0, prev_row1;
     // scaled mode (badly scaled input): per column c of G an exponent e_c
     // with ||g_c|| in [2^e_c, 2^(e_c+1)); the Gram kernel forms
     // D^-1 H D^-1 (D = diag(2^e_c)), the inner kernel works on R D^-1 and
