@@ -6,12 +6,15 @@ for every new handle (jsvd_set_tuning).
 
 Tuned:
   * the block width w of the dense SVD / HSVD, over w in {16, 32, 64}, on seeded
-    N(0,1) square matrices of several orders n: the table maps each measured
-    n to the fastest w (a problem takes the entry of the first measured n
+    N(0,1) square matrices of several orders n, by the time per sweep with and
+    without V (on one matrix the number of sweeps differs by chance): the table
+    maps each measured n to the fastest w (a problem takes the entry of the first measured n
     that is >= its n, or the last one);
   * for that w and n, the tile shapes of the p-step kernels: the number of
     workgroups of a Gram launch (its row splits) and of an update launch
-    (its row chunks per pivot pair), over a small grid;
+    (its row chunks per pivot pair), over a small grid, by the time per sweep;
+    the choice of the order before is kept where it has the same w and is within
+    1% of the best;
   * the split of the batched kernel's 32 half waves between rotating G and
     applying the rotations to V, on the 10000-problem ragged batch (n 8..128,
     m = n + 0..64, the synthetic stand-in of the batched workload), with
@@ -33,7 +36,7 @@ import numpy as np
 
 from . import inputs
 
-DENSE_ORDERS = (256, 512, 1024, 2048, 3072, 4096, 8192)
+DENSE_ORDERS = (256, 512, 1024, 1536, 2048, 3072, 4096, 6144, 8192)
 WIDTHS = (16, 32, 64)
 GRAM_WG = (256, 512, 1024)
 UPDATE_WG = (512, 1024, 2048)
@@ -41,15 +44,17 @@ G_GROUPS = (8, 12, 16, 20, 24)
 BLOCK_MIN_N = (33, 49, 65, 81, 97, 257)  # 257: no problem blocked
 
 
-def _time_dense(B, A, w, reps=2):
+def _time_dense(B, A, w, reps=2, want_v=True):
+    """Seconds per sweep."""
     import torch
     best = None
     for it in range(reps + 1):
         torch.cuda.synchronize()
-        _, _, _, info = B.gesvd(A, block_w=w)
+        _, _, _, info = B.gesvd(A, block_w=w, want_v=want_v)
         torch.cuda.synchronize()
         if it:
-            best = info["seconds"] if best is None else min(best, info["seconds"])
+            t = info["seconds"] / info["sweeps"]
+            best = t if best is None else min(best, t)
     return best
 
 
@@ -64,7 +69,7 @@ def tune_dense(orders=DENSE_ORDERS, widths=WIDTHS, gram_wg=GRAM_WG, update_wg=UP
     for n in orders:
         A = torch.from_numpy(inputs.gaussian(n, n, inputs.rng(seed + n))).cuda()
         B.set_tuning(dev, None)
-        times = {w: _time_dense(B, A, w) for w in widths}
+        times = {w: _time_dense(B, A, w) + _time_dense(B, A, w, want_v=False) for w in widths}
         best = min(times, key=times.get)
         shapes = {}
         for g in gram_wg:
@@ -74,8 +79,12 @@ def tune_dense(orders=DENSE_ORDERS, widths=WIDTHS, gram_wg=GRAM_WG, update_wg=UP
                 shapes[(g, u)] = _time_dense(B, A, best)
         B.set_tuning(dev, None)
         g_best, u_best = min(shapes, key=shapes.get)
-        rows.append({"n": n, "times_s": {str(w): t for w, t in times.items()}, "block_w": best,
-                     "shape_times_s": {f"{g}/{u}": t for (g, u), t in shapes.items()},
+        if rows and rows[-1]["block_w"] == best:
+            before = (rows[-1]["gram_wg"], rows[-1]["update_wg"])
+            if shapes[before] <= 1.01 * shapes[(g_best, u_best)]:
+                g_best, u_best = before
+        rows.append({"n": n, "sweep_s_v_and_no_v": {str(w): t for w, t in times.items()}, "block_w": best,
+                     "shape_sweep_s": {f"{g}/{u}": t for (g, u), t in shapes.items()},
                      "gram_wg": g_best, "update_wg": u_best})
         print(json.dumps(rows[-1]), flush=True)
     return rows

@@ -266,12 +266,13 @@ jsvd_opts defaults() {
 }
 
 // Block width and inner sweep limit when the caller leaves them to the
-// library (measured on MI355X: 2w = 64 pays off once the p-steps' HBM
-// traffic dominates, from n of about 3000; the block-oriented variant,
-// M_s = 1, was faster than the full block one at every size measured).
+// library (measured on MI355X: 2w = 64 halves the p-steps and pays off above n
+// = 1536: 3.7 ms per sweep there with either w, 2.3 against 2.1 ms at 1024, 5.4
+// against 6.0 ms at 2048; the block-oriented variant, M_s = 1, was faster than
+// the full block one at every size measured).
 int choose_w(int64_t m, int64_t n) {
     (void)m;
-    return n >= 3072 ? 32 : 16;
+    return n > 1536 ? 32 : 16;
 }
 
 int choose_inner_sweeps(int64_t m, int64_t n) {
@@ -283,7 +284,8 @@ int choose_inner_sweeps(int64_t m, int64_t n) {
 // Block width and kernel tile shapes of a solve: w is the caller's, else
 // the handle's tuning table, else the built-in size rule; the shapes
 // (workgroups per Gram and update launch) come from the tuning entry of the
-// problem's size, else the built-in 512 and 1024.
+// problem's size, else the built-in 256 (2048: 48.4 ms against 51.2 with 512)
+// and 1024.
 struct Shapes {
     int w, gram_wg, update_wg;
 };
@@ -298,7 +300,7 @@ Shapes pick_shapes(const jsvd_handle_s *h, const jsvd_opts &o, int64_t m, int64_
         sh.update_wg = h->tuning.update_wg[i];
     }
     if (!sh.w) sh.w = choose_w(m, n);
-    if (!sh.gram_wg) sh.gram_wg = 512;
+    if (!sh.gram_wg) sh.gram_wg = 256;
     if (!sh.update_wg) sh.update_wg = 1024;
     return sh;
 }
