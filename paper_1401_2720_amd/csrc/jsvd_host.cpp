@@ -436,6 +436,54 @@ int64_t quad_chunk_rows(int64_t half_rows, int nquads, int npairs, int cu) {
     return best;
 }
 
+// The whole solve in one launch when the matrix is one pivot pair (order 2,
+// w = 16): 1 if done, 0 if the scale of the input is to be looked at first, or
+// the negative of an error status.
+int solve_one_pair(jsvd_handle_s *h, int64_t m, int64_t n, double *A, int64_t lda, double *S,
+                   double *V, int64_t ldv, int64_t n_plus, const jsvd_opts &o, jsvd_info &inf,
+                   int *status) {
+    StepArgs a{};
+    const int2 *blk = nullptr;
+    const unsigned char *inner = nullptr;
+    int rc = 0;
+    if ((rc = get_block_table(h, 2, o.strategy, &blk))) return -rc;
+    if ((rc = get_inner_table(h, 32, o.strategy, &inner))) return -rc;
+    a.G = A;
+    a.ldg = lda;
+    a.m = m;
+    a.V = o.want_v ? V : nullptr;
+    a.ldv = ldv;
+    a.n = n;
+    a.w = 16;
+    a.n_plus = (int)n_plus;
+    a.pairs = blk;
+    a.npairs = 1;
+    a.inner_tbl = inner;
+    a.max_inner_sweeps = o.max_inner_sweeps > 0 ? o.max_inner_sweeps : choose_inner_sweeps(m, n);
+    a.S = S;
+    a.solve_sweeps = o.max_sweeps;
+    a.solve_check = o.scaled == 0;
+    a.solve_sort = o.sort;
+    a.counters = h->host_counters;  // pinned: written by the kernel
+    if (launch_solve(a, h->stream) != hipSuccess) return -JSVD_HIP_ERROR;
+    if (hipStreamSynchronize(h->stream) != hipSuccess) return -JSVD_HIP_ERROR;
+    const unsigned long long *c = h->host_counters;
+    if (c[C_SOLVE] & kSolveLeft) return 0;
+    inf.block_w = 16;
+    inf.n_blocks = 2;
+    inf.rank = (int32_t)n;
+    inf.sweeps = (int32_t)(c[C_SOLVE] & (kSolveConverged - 1));
+    inf.rotations = (int64_t)c[C_ROT];
+    inf.proper_rotations = (int64_t)c[C_PROPER];
+    inf.inner_sweeps = (int64_t)c[C_INNER_SW];
+    inf.pair_updates = (int64_t)c[C_UPDATES];
+    inf.chol_breakdowns = (int32_t)c[C_BREAKDOWN];
+    inf.hyp_clamps = (int32_t)c[C_CLAMP];
+    inf.converged = (c[C_SOLVE] & kSolveConverged) ? 1 : 0;
+    *status = c[C_NONFINITE] ? JSVD_NONFINITE : inf.converged ? JSVD_OK : JSVD_NOT_CONVERGED;
+    return 1;
+}
+
 // The solver shared by the SVD and the hyperbolic SVD.  A holds G with J
 // already partitioned (columns [0, n_plus) positive).
 int solve(jsvd_handle_s *h, int64_t m, int64_t n, double *A, int64_t lda, double *S, double *V,
@@ -444,6 +492,40 @@ int solve(jsvd_handle_s *h, int64_t m, int64_t n, double *A, int64_t lda, double
     const auto t0 = std::chrono::steady_clock::now();
     hipStream_t st = h->stream;
     int rc = 0;
+    jsvd_info inf{};
+    std::memset(&inf, 0, sizeof inf);
+    // rows of V back to the caller's order of columns (HSVD)
+    auto restore_rows = [&](char *ws, const Layout &L) {
+        double *tmp = reinterpret_cast<double *>(ws + L.tmp);
+        int *pin = reinterpret_cast<int *>(ws + L.perm_in);
+        HIP_TRY(hipMemcpyAsync(pin, perm_in_host, n * sizeof(int), hipMemcpyHostToDevice, st));
+        HIP_TRY(hipMemcpy2DAsync(tmp, n * sizeof(double), V, ldv * sizeof(double),
+                                 n * sizeof(double), n, hipMemcpyDeviceToDevice, st));
+        HIP_TRY(launch_scatter_rows(tmp, n, V, ldv, n, n, pin, st));
+        return (int)JSVD_OK;
+    };
+    auto done = [&](int status) {
+        const auto t1 = std::chrono::steady_clock::now();
+        inf.seconds = std::chrono::duration<double>(t1 - t0).count();
+        if (info) *info = inf;
+        return status;
+    };
+    // one pivot pair: the whole solve in one launch
+    if (n <= 32 && m <= kSolveMaxM && o.scaled != 2 && o.factorize != 1 && !h->timing &&
+        pick_shapes(h, o, m, n).w == 16) {
+        int status = JSVD_OK;
+        const int r = solve_one_pair(h, m, n, A, lda, S, V, ldv, n_plus, o, inf, &status);
+        if (r < 0) return -r;
+        if (r == 1) {
+            if (o.want_v && hsvd && perm_in_host) {
+                const Layout L = plan(m, n, 32, 1, 1, hsvd);
+                if ((rc = ensure_workspace(h, L.total))) return rc;
+                if ((rc = restore_rows(static_cast<char *>(h->ws), L))) return rc;
+                HIP_TRY(hipStreamSynchronize(st));
+            }
+            return done(status);
+        }
+    }
     // scaled mode (opts.scaled: 2 on, 1 off, 0 when G is badly scaled)
     bool scaled = o.scaled == 2;
     if (o.scaled != 1) {
@@ -573,8 +655,6 @@ int solve(jsvd_handle_s *h, int64_t m, int64_t n, double *A, int64_t lda, double
 
     if (want_v) HIP_TRY(launch_init_identity(V, ldv, n, st));
 
-    jsvd_info inf{};
-    std::memset(&inf, 0, sizeof inf);
     inf.block_w = w;
     inf.scaled = scaled ? 1 : 0;
     inf.n_blocks = order;
@@ -733,18 +813,9 @@ int solve(jsvd_handle_s *h, int64_t m, int64_t n, double *A, int64_t lda, double
     } else {
         HIP_TRY(launch_gather_cols(A, lda, A, lda, m, n, nullptr, s_tmp, S, st));
     }
-    if (want_v && hsvd && perm_in_host) {
-        int *pin = reinterpret_cast<int *>(ws + L.perm_in);
-        HIP_TRY(hipMemcpyAsync(pin, perm_in_host, n * sizeof(int), hipMemcpyHostToDevice, st));
-        HIP_TRY(hipMemcpy2DAsync(tmp, n * sizeof(double), V, ldv * sizeof(double),
-                                 n * sizeof(double), n, hipMemcpyDeviceToDevice, st));
-        HIP_TRY(launch_scatter_rows(tmp, n, V, ldv, n, n, pin, st));
-    }
+    if (want_v && hsvd && perm_in_host && (rc = restore_rows(ws, L))) return rc;
     HIP_TRY(hipStreamSynchronize(st));
-    const auto t1 = std::chrono::steady_clock::now();
-    inf.seconds = std::chrono::duration<double>(t1 - t0).count();
-    if (info) *info = inf;
-    return status;
+    return done(status);
 }
 
 

@@ -560,7 +560,64 @@ struct JacCfg {
     }
 };
 
-template <int BW, bool HYP>
+// The Gram matrix of a pivot pair of 32 columns from G itself, by all eight
+// waves: entry (i, j), i <= j, of thread-indexed sums s[].  part: 3072 doubles
+// of LDS; ends with a barrier, after which they are free.
+template <int EPT>
+__device__ __forceinline__ void pair_gram32(const StepArgs &a, int2 pq, double *part,
+                                            double (&s)[EPT]) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int i16 = lane & 15, grp = lane >> 4;
+    const int64_t cp = (int64_t)pq.x * a.w + i16, cq = (int64_t)pq.y * a.w + i16;
+    d4 g[3] = {d4{0.0, 0.0, 0.0, 0.0}, d4{0.0, 0.0, 0.0, 0.0}, d4{0.0, 0.0, 0.0, 0.0}};
+    for (int64_t r = 16 * wave + 4 * grp; r - 4 * grp < a.m; r += 128) {
+        double x[4], y[4];
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            x[v] = (r + v < a.m && cp < a.n) ? a.G[r + v + cp * a.ldg] : 0.0;
+            y[v] = (r + v < a.m && cq < a.n) ? a.G[r + v + cq * a.ldg] : 0.0;
+        }
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            g[0] = mfma16(x[v], x[v], g[0]);
+            g[1] = mfma16(x[v], y[v], g[1]);
+            g[2] = mfma16(y[v], y[v], g[2]);
+        }
+    }
+    // waves 4 to 7 add to 0 to 3, whose four sums are added entry by entry
+    double *mine = part + (wave & 3) * 768 + lane;
+    if (wave >= 4)
+#pragma unroll
+        for (int t = 0; t < 3; ++t)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) mine[(4 * t + v) * 64] = g[t][v];
+    __syncthreads();
+    if (wave < 4)
+#pragma unroll
+        for (int t = 0; t < 3; ++t)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) mine[(4 * t + v) * 64] += g[t][v];
+    __syncthreads();
+    const int j = threadIdx.x % 32;
+#pragma unroll
+    for (int u = 0; u < EPT; ++u) {
+        const int i = threadIdx.x / 32 + u * (32 / EPT);
+        s[u] = 0.0;
+        if (i <= j) {
+            const int t = i / 16 + j / 16, v = (i & 15) >> 2, l = (i & 3) * 16 + (j & 15);
+            const double *e = part + (4 * t + v) * 64 + l;
+            s[u] = (e[0] + e[768]) + (e[2 * 768] + e[3 * 768]);
+        }
+    }
+    __syncthreads();
+}
+
+// SOLVE: one workgroup does the whole solve of a single pivot pair (n <= 32,
+// w = 16), G and V in global memory (cache): per sweep the Gram matrix, this
+// kernel's inner sweeps and the updates of G and V, then the singular values,
+// U and the order.  Bound by the chain of the inner sweep (17 us of about 20
+// per sweep); four launches, a copy and a wait per sweep take 58 us.
+template <int BW, bool HYP, bool SOLVE = false>
 __global__ __launch_bounds__(JacCfg<BW>::kThreads) void jacobi_kernel(StepArgs a) {
     using Cfg = JacCfg<BW>;
     constexpr int NT = Cfg::kThreads, NWAVES = NT / 64;
@@ -583,8 +640,9 @@ __global__ __launch_bounds__(JacCfg<BW>::kThreads) void jacobi_kernel(StepArgs a
     __shared__ unsigned dst[2][NP];          // next positions (times 8) of new p | q << 16
     __shared__ int flags;                    // 1: not orthogonal, 2: a NaN or infinity in H
     __shared__ int rots;                     // rotations of the inner sweep
+    __shared__ int total[2];                 // SOLVE: rotations, proper ones of the sweep
 
-    if (blockIdx.x >= a.npairs) {
+    if (!SOLVE && blockIdx.x >= a.npairs) {
         // V <- V V'_pq of an earlier p-step, as in inner_kernel
         const int idx = blockIdx.x - a.npairs;
         const int vpair = idx / a.prev_chunks, chunk = idx % a.prev_chunks;
@@ -627,8 +685,38 @@ __global__ __launch_bounds__(JacCfg<BW>::kThreads) void jacobi_kernel(StepArgs a
     int pi[EPT];
 #pragma unroll
     for (int u = 0; u < EPT; ++u) pi[u] = pos0[ei + u * (NT / BW)];
+    unsigned long long sum[C_COUNT] = {};  // SOLVE: the counters, in wave 0
+    if constexpr (SOLVE) {
+        if (a.solve_check) {
+            // entries so large or columns so small that the norms could leave
+            // the range of the unscaled method: the host decides
+            bool odd = false;
+            for (int64_t c = wave; c < a.n; c += NWAVES) {
+                double mx = 0.0;
+                for (int64_t r = lane; r < a.m; r += 64) {
+                    const double x = fabs(a.G[r + c * a.ldg]);
+                    odd = odd || !(x <= 0x1p400);
+                    mx = x > mx ? x : mx;
+                }
+                odd = odd || (__builtin_amdgcn_ballot_w64(mx > 0.0) != 0 &&
+                              __builtin_amdgcn_ballot_w64(mx >= 0x1p-400) == 0);
+            }
+            if (__syncthreads_or(odd)) {
+                if (tid == 0) a.counters[C_SOLVE] = kSolveLeft;
+                return;
+            }
+        }
+        if (a.V)
+            for (int64_t e = tid; e < a.n * a.n; e += NT)
+                a.V[e % a.n + e / a.n * a.ldv] = e % a.n == e / a.n ? 1.0 : 0.0;
+    }
+    bool table_due = true;
+    for (int block_sweep = 0; block_sweep < (SOLVE ? a.solve_sweeps : 1); ++block_sweep) {
     const double *hp = a.hpart + (size_t)pair * a.splits * BW * BW;
     double s[EPT];
+    if constexpr (SOLVE) {
+        pair_gram32<EPT>(a, pq, arena, s);
+    } else {
 #pragma unroll
     for (int u = 0; u < EPT; ++u) s[u] = 0.0;
     for (int s0 = 0; s0 < a.splits; s0 += 8) {
@@ -646,7 +734,8 @@ __global__ __launch_bounds__(JacCfg<BW>::kThreads) void jacobi_kernel(StepArgs a
             for (int u = 0; u < EPT; ++u)
                 if (s0 + sp < a.splits) s[u] += hv[sp][u];
     }
-    if (2 * tid < NS * NP) {
+    }
+    if (table_due && 2 * tid < NS * NP) {
         auto put = [&](int e, unsigned lo, unsigned hi) {
             tbl[e] = make_uint2(lo, hi);
             // where the sent column goes (bytes in xch); bit 31: the kept
@@ -656,6 +745,7 @@ __global__ __launch_bounds__(JacCfg<BW>::kThreads) void jacobi_kernel(StepArgs a
         put(2 * tid, tv.x, tv.y);
         put(2 * tid + 1, tv.z, tv.w);
     }
+    table_due = false;
     if (tid == 0) flags = 0;
 
     // ---- H_pq; padding columns become unit vectors orthogonal to everything
@@ -700,6 +790,12 @@ __global__ __launch_bounds__(JacCfg<BW>::kThreads) void jacobi_kernel(StepArgs a
     }
     __syncthreads();
     if (flags != 1) {  // nothing to do, or a NaN or infinity in H
+        if constexpr (SOLVE) {
+            const bool nonfinite = flags == 3;
+            sum[C_NONFINITE] += nonfinite;
+            sum[C_SOLVE] += 1 + (nonfinite ? 0 : kSolveConverged);
+            break;
+        }
         if (tid == 0) {
             a.pair_rot[pair] = 0;
             if (flags == 3) atomicAdd(&a.counters[C_NONFINITE], 1ull);
@@ -712,7 +808,7 @@ __global__ __launch_bounds__(JacCfg<BW>::kThreads) void jacobi_kernel(StepArgs a
     const bool on_h = wave >= Cfg::kHFirst && wave < Cfg::kHFirst + Cfg::kHCount;
     const int vw = __builtin_amdgcn_readfirstlane(Cfg::v_wave(wave));
     // waves without a role end here: barriers wait for the others only
-    if (!on_rot && !on_h && vw < 0) return;
+    if (!SOLVE && !on_rot && !on_h && vw < 0) return;
     constexpr int LIVE = 64 * (1 + Cfg::kHCount + Cfg::kVCount);
     const int ltid = lane + 64 * (on_rot ? 0 : on_h ? wave : 1 + Cfg::kHCount + vw);
     char *const hb = reinterpret_cast<char *>(&H[0][0]);
@@ -987,6 +1083,34 @@ __global__ __launch_bounds__(JacCfg<BW>::kThreads) void jacobi_kernel(StepArgs a
         }
     }
 
+    if constexpr (SOLVE) {
+        double *const vp = &xch[0][0];  // both halves: V', column-major
+        if (vw >= 0) put_v(vp);
+        if (on_rot) {
+            const int brk = __builtin_popcountll(__builtin_amdgcn_ballot_w64(!(diag[k] > 0.0)) & lanes) +
+                            __builtin_popcountll(__builtin_amdgcn_ballot_w64(!(diag[k + NP] > 0.0)) & lanes);
+            sum[C_ROT] += rot_total;
+            sum[C_PROPER] += proper_total;
+            sum[C_CLAMP] += clamp_total;
+            sum[C_INNER_SW] += sweeps;
+            sum[C_BREAKDOWN] += brk;
+            sum[C_UPDATES] += rot_total != 0;
+            if (lane == 0) {
+                total[0] = rot_total;
+                total[1] = proper_total;
+            }
+        }
+        __syncthreads();
+        const bool converged = total[1] == 0;
+        if (total[0]) {
+            update_rows<BW, NWAVES, 1>(a.G, a.ldg, 0, a.m, pq, a.w, a.n, vp, arena);
+            __syncthreads();
+            if (a.V) update_rows<BW, NWAVES, 1>(a.V, a.ldv, 0, a.n, pq, a.w, a.n, vp, arena);
+            __syncthreads();
+        }
+        sum[C_SOLVE] += 1 + (converged ? kSolveConverged : 0);
+        if (converged) break;
+    } else {
     // ---- write V'_pq and the counts
     if (vw >= 0) put_v(a.vprime + (size_t)pair * BW * BW);
     if (on_rot) {
@@ -1003,6 +1127,59 @@ __global__ __launch_bounds__(JacCfg<BW>::kThreads) void jacobi_kernel(StepArgs a
             if (brk) atomicAdd(&a.counters[C_BREAKDOWN], (unsigned long long)brk);
             if (rot_total) atomicAdd(&a.counters[C_UPDATES], 1ull);
         }
+    }
+    }
+    }
+
+    if constexpr (SOLVE) {
+        // ---- sigma_j = ||g_j||, the output order, U = G / sigma and V in it
+        __syncthreads();
+        double *const nrm = arena;
+        int *const perm = reinterpret_cast<int *>(arena + 32);
+        for (int64_t c = wave; c < a.n; c += NWAVES) {
+            double q = 0.0;
+            for (int64_t r = lane; r < a.m; r += 64) q = fma(a.G[r + c * a.ldg], a.G[r + c * a.ldg], q);
+#pragma unroll
+            for (int d = 32; d > 0; d /= 2) q += __shfl_xor(q, d, 64);
+            if (lane == 0) nrm[c] = sqrt(q);
+        }
+        __syncthreads();
+        if (tid < a.n) {
+            int rank = tid;
+            if (a.solve_sort) {
+                // as rank_kernel: +1 columns by non-increasing sigma, then -1
+                // columns by non-decreasing sigma, NaN as -infinity
+                const bool pos = tid < a.n_plus;
+                const int lo = pos ? 0 : a.n_plus, hi = pos ? a.n_plus : (int)a.n;
+                auto key = [&](int i) { return nrm[i] != nrm[i] ? -INFINITY : nrm[i]; };
+                const double kj = key(tid);
+                rank = lo;
+                for (int i = lo; i < hi; ++i) {
+                    const double ki = key(i);
+                    if ((pos ? ki > kj : ki < kj) || (ki == kj && i < tid)) ++rank;
+                }
+            }
+            perm[rank] = tid;
+        }
+        __syncthreads();
+        if (tid < a.n) a.S[tid] = nrm[perm[tid]];
+        auto reorder = [&](double *X, int64_t ldx, int64_t rows, bool scale) {
+            for (int64_t r = tid; r < rows; r += NT) {
+                double x[BW];
+#pragma unroll
+                for (int c = 0; c < BW; ++c) x[c] = c < a.n ? X[r + perm[c] * ldx] : 0.0;
+#pragma unroll
+                for (int c = 0; c < BW; ++c)
+                    if (c < a.n) {
+                        const double sc = scale ? nrm[perm[c]] : 1.0;
+                        X[r + c * ldx] = scale ? (sc > 0.0 ? x[c] / sc : 0.0) : x[c];
+                    }
+            }
+        };
+        reorder(a.G, a.ldg, a.m, true);
+        if (a.V && a.solve_sort) reorder(a.V, a.ldv, a.n, false);
+        if (tid == 0)
+            for (int c = 0; c < C_COUNT; ++c) a.counters[c] = sum[c];
     }
 }
 
@@ -1214,6 +1391,15 @@ __global__ __launch_bounds__(kW128Threads) void inner128_kernel(StepArgs a) {
 }
 
 }  // namespace
+
+hipError_t launch_solve(const StepArgs &a, hipStream_t s) {
+    const dim3 nt(JacCfg<32>::kThreads);
+    if (a.n_plus < a.n)
+        hipLaunchKernelGGL((jacobi_kernel<32, true, true>), dim3(1), nt, 0, s, a);
+    else
+        hipLaunchKernelGGL((jacobi_kernel<32, false, true>), dim3(1), nt, 0, s, a);
+    return hipGetLastError();
+}
 
 hipError_t launch_inner(int bw, const StepArgs &a, hipStream_t s) {
     if (bw == 128) {

@@ -58,8 +58,12 @@ enum Counter {
     C_INNER_SW = 4,  // inner sweeps
     C_UPDATES = 5,   // pivot block-pairs with a transformation to apply
     C_NONFINITE = 6, // NaN met in a pivot Gram matrix
+    C_SOLVE = 7,     // launch_solve: block sweeps done, or one of
     C_COUNT = 8
 };
+
+constexpr unsigned long long kSolveConverged = 1ull << 32;  // added to the sweeps
+constexpr unsigned long long kSolveLeft = 1ull << 33;       // nothing done: scale suspected
 
 // ------------------------------------------------------- one p-step's launch
 struct StepArgs {
@@ -121,6 +125,11 @@ struct StepArgs {
     const int64_t *btbl_off;
     const unsigned char *btbls;
     const unsigned char *bjac;  // position_tables' of order 32
+    // the whole solve of a single pivot pair in one launch (launch_solve)
+    double *S;          // singular values
+    int solve_sweeps;   // sweep limit
+    int solve_check;    // 1: leave badly scaled input alone
+    int solve_sort;     // 1: order the columns by sigma
     // the update fused with the next p-step's Gram kernel: the quads of this
     // p-step (8 ints each: old pairs ia, ib, new pairs jx, jy, blocks a0 of
     // ia and b0 of ib that go to jx, two unused) and the next p-step's pairs
@@ -132,6 +141,13 @@ hipError_t launch_gram(int bw, const StepArgs &a, hipStream_t s);
 hipError_t launch_qrfac(int bw, const StepArgs &a, hipStream_t s);
 hipError_t launch_inner(int bw, const StepArgs &a, hipStream_t s);
 hipError_t launch_update(int bw, const StepArgs &a, hipStream_t s);
+// The whole solve when n <= 32 is one pivot pair (w = 16): sweeps, singular
+// values, U and the output order.  counters (C_COUNT, any memory the device can
+// write) are set, C_SOLVE included.
+hipError_t launch_solve(const StepArgs &a, hipStream_t s);
+// Its largest number of rows: one CU streams 768 x 32 in about 265 us for the solve
+// (launches per sweep: 306 us; 24 x 17: 131 against 255; 1024 x 32: 315 against 306).
+constexpr int64_t kSolveMaxM = 768;
 hipError_t launch_fused(int nquads, const StepArgs &a, hipStream_t s);
 
 // ------------------------------------------------------ batched small SVDs
