@@ -26,6 +26,7 @@ namespace {
 
 constexpr int kNb = kQrPanel;      // panel width
 constexpr int kQT = 256;           // threads per workgroup of the panel kernel
+constexpr int kQTWide = 512;       // of its wide variant
 constexpr int kRpt = 2;            // panel rows per thread, at most
 
 // Grid-wide barrier among resident workgroups: monotonic arrival counter,
@@ -62,44 +63,54 @@ __device__ __forceinline__ bool grid_sync(unsigned *bar, unsigned target, int *a
     return s_ok != 0;
 }
 
-// Sums of the kNb values v[] over the workgroup's 256 threads, in a fixed
-// order: red[c][t] <- v[c] of thread t; 8 segments of 32 threads summed
-// sequentially, then the 8 segment sums.  Result in out[c] for c < nv.
+// Sums of the kNb values v[] over the workgroup's QT threads, in a fixed
+// order: red[c][t] <- v[c] of thread t; QT / 32 segments of 32 threads summed
+// sequentially, then the segment sums.  Result in out[c].
 // Thread t sums segment t / 32 of column t mod 32, so that the 16 lanes of
 // a wave that read LDS together read 16 columns (distinct banks), and seg
-// is padded to 9 for the same reason.
-__device__ __forceinline__ void wg_sum(const double (&v)[kNb], int nv, double (*red)[kQT + 1], double (*seg)[9],
-                       double *out) {
-    static_assert(kNb == 32 && kQT == 256, "32 columns, 8 segments of 32 threads");
+// is padded by one for the same reason.
+template <int QT>
+__device__ __forceinline__ void wg_sum(const double (&v)[kNb], double (*red)[QT + 1],
+                                       double (*seg)[QT / 32 + 1], double *out) {
+    static_assert(kNb == 32, "a segment per 32 threads");
     const int t = threadIdx.x;
 #pragma unroll
-    for (int c = 0; c < kNb; ++c)
-        if (c < nv) red[c][t] = v[c];
+    for (int c = 0; c < kNb; ++c) red[c][t] = v[c];
     __syncthreads();
     {
         const int c = t & 31, sg = t >> 5;
-        if (c < nv) {
-            double s = 0.0;
-            for (int i = 0; i < 32; ++i) s += red[c][sg * 32 + i];
-            seg[c][sg] = s;
-        }
+        double s = 0.0;
+#pragma unroll 8
+        for (int i = 0; i < 32; ++i) s += red[c][sg * 32 + i];
+        seg[c][sg] = s;
     }
     __syncthreads();
-    if (t < nv) {
+    if (t < kNb) {
         double s = 0.0;
-        for (int i = 0; i < 8; ++i) s += seg[t][i];
+#pragma unroll
+        for (int i = 0; i < QT / 32; ++i) s += seg[t][i];
         out[t] = s;
     }
     __syncthreads();
 }
 
-__global__ __launch_bounds__(kQT, 1) void qr_panel_kernel(QrPanelArgs a) {
-    __shared__ double red[kNb][kQT + 1];
-    __shared__ double seg[kNb][9];
+// QT threads per workgroup, kRpt rows per thread in registers.  The columns move
+// one place to the left with each column's update, so that the current column is
+// always x[.][0] and no register is picked out by k; a finished column goes to
+// memory at once.  Rows that take no part (above the pivot, past the end) get a
+// factor of zero instead of a branch.  A single workgroup (rows <= 2 QT) needs no
+// grid barrier: the sums and the pivot row stay in LDS.  Bound by the chain per
+// column: a panel of 300 rows takes 64 us (with
+// the current column selected by k 163 us), of 3000 rows 121 (170), of 8192 rows
+// 166 (213).
+template <int QT>
+__global__ __launch_bounds__(QT, 1) void qr_panel_kernel(QrPanelArgs a) {
+    __shared__ double red[kNb][QT + 1];
+    __shared__ double seg[kNb][QT / 32 + 1];
     __shared__ double wsum[kNb];
-    __shared__ double gsum[kNb];
+    __shared__ double gsum[kNb];   // index c here: column k + c
     __shared__ double s_prow[kNb];
-    __shared__ double s_w[kNb];   // v^T a_c of the current column's reflector
+    __shared__ __align__(16) double s_w[kNb + 2];  // v^T a_c of the current column's reflector
     const int wg = blockIdx.x, t = threadIdx.x;
     const int64_t rows = a.m - a.j;                       // panel rows j .. m-1
     const int64_t chunk = (rows + a.nwg - 1) / a.nwg;     // rows per workgroup
@@ -113,67 +124,58 @@ __global__ __launch_bounds__(kQT, 1) void qr_panel_kernel(QrPanelArgs a) {
     int64_t rr[kRpt];
 #pragma unroll
     for (int q = 0; q < kRpt; ++q) {
-        rr[q] = r_beg + t + (int64_t)q * kQT;
+        rr[q] = r_beg + t + (int64_t)q * QT;
         const bool in = rr[q] < r_end;
 #pragma unroll
         for (int c = 0; c < kNb; ++c) x[q][c] = (in && c < nb) ? W[rr[q] + (a.j + c) * ldw] : 0.0;
     }
+    if (t < 2) s_w[kNb + t] = 0.0;
 
-    // Column k of the panel is picked out of the register arrays by
-    // selection over the (unrolled) column index, so that the arrays stay in
-    // registers while k runs over the panel.
     for (int k = 0; k < nb; ++k) {
         const int64_t pr = a.j + k;  // pivot row
         const int par = k & 1;
-        double xk[kRpt];
-#pragma unroll
-        for (int q = 0; q < kRpt; ++q) {
-            xk[q] = 0.0;
-#pragma unroll
-            for (int c = 0; c < kNb; ++c) xk[q] = (c == k) ? x[q][c] : xk[q];
-        }
-        // partial sums over own rows below the pivot: column k with columns k .. nb-1
-        // (also formed, and not used, for the columns left of k)
+        // partial sums over own rows below the pivot: column k with columns k ..
         double ps[kNb];
 #pragma unroll
         for (int c = 0; c < kNb; ++c) ps[c] = 0.0;
 #pragma unroll
         for (int q = 0; q < kRpt; ++q) {
-            if (rr[q] > pr && rr[q] < r_end) {
+            const double xk = rr[q] > pr ? x[q][0] : 0.0;  // zero past the end
 #pragma unroll
-                for (int c = 0; c < kNb; ++c) ps[c] = fma(xk[q], x[q][c], ps[c]);
-            }
+            for (int c = 0; c < kNb; ++c) ps[c] = fma(xk, x[q][c], ps[c]);
             if (rr[q] == pr && rr[q] < r_end) {
 #pragma unroll
-                for (int c = 0; c < kNb; ++c)
-                    if (c >= k) a.prow[par * kNb + c] = x[q][c];
+                for (int c = 0; c < kNb; ++c) s_prow[c] = x[q][c];
+                if (a.nwg > 1)
+#pragma unroll
+                    for (int c = 0; c < kNb; ++c) a.prow[par * kNb + c] = x[q][c];
             }
         }
-        wg_sum(ps, nb, red, seg, wsum);
-        if (t < nb) a.partials[((size_t)par * a.nwg + wg) * kNb + t] = wsum[t];
-        if (!grid_sync(a.bar, (unsigned)(a.nwg * (k + 1)), a.abort_flag)) return;
-        // all workgroups: totals in workgroup order, the pivot row, the
-        // reflector.  The nwg x nb partial sums (nwg <= 64) and the pivot row
-        // are loaded by all threads at once into LDS (one memory round trip),
-        // then each column's partials are added in workgroup order.
-        {
+        wg_sum<QT>(ps, red, seg, a.nwg == 1 ? gsum : wsum);
+        if (a.nwg > 1) {
+            if (t < kNb) a.partials[((size_t)par * a.nwg + wg) * kNb + t] = wsum[t];
+            if (!grid_sync(a.bar, (unsigned)(a.nwg * (k + 1)), a.abort_flag)) return;
+            // all workgroups: totals in workgroup order, the pivot row, the
+            // reflector.  The nwg x nb partial sums (nwg <= 64) and the pivot
+            // row are loaded by all threads at once into LDS (one memory round
+            // trip), then each column's partials are added in workgroup order.
             const int c = t & 31;
 #pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                const int w = (t >> 5) + 8 * i;
-                if (c < nb && w < a.nwg) red[c][w] = a.partials[((size_t)par * a.nwg + w) * kNb + c];
+            for (int i = 0; i < 64 * 32 / QT; ++i) {
+                const int w = (t >> 5) + QT / 32 * i;
+                if (w < a.nwg) red[c][w] = a.partials[((size_t)par * a.nwg + w) * kNb + c];
             }
-            if (t < nb) s_prow[t] = a.prow[par * kNb + t];
+            if (t < kNb) s_prow[t] = a.prow[par * kNb + t];
+            __syncthreads();
+            if (t < kNb) {
+                double sum = 0.0;
+                for (int w = 0; w < a.nwg; ++w) sum += red[t][w];
+                gsum[t] = sum;
+            }
+            __syncthreads();
         }
-        __syncthreads();
-        if (t < nb) {
-            double sum = 0.0;
-            for (int w = 0; w < a.nwg; ++w) sum += red[t][w];
-            gsum[t] = sum;
-        }
-        __syncthreads();
-        const double alpha = s_prow[k];
-        const double xn2 = gsum[k];  // squared norm below the pivot
+        const double alpha = s_prow[0];
+        const double xn2 = gsum[0];  // squared norm below the pivot
         double tau = 0.0, beta = alpha, scal = 0.0;
         if (xn2 > 0.0) {
             beta = -copysign(sqrt(fma(alpha, alpha, xn2)), alpha);
@@ -181,66 +183,60 @@ __global__ __launch_bounds__(kQT, 1) void qr_panel_kernel(QrPanelArgs a) {
             scal = 1.0 / (alpha - beta);
         }
         // v^T a_c for the columns the reflection changes, zero for the others
-        if (t < kNb) s_w[t] = (t > k && t < nb && tau != 0.0) ? fma(scal, gsum[t], s_prow[t]) : 0.0;
+        if (t < kNb)
+            s_w[t] = (t > 0 && t < nb - k && tau != 0.0) ? fma(scal, gsum[t], s_prow[t]) : 0.0;
         __syncthreads();
         if (wg == 0 && t == 0) a.tau[a.j + k] = tau;
-        // rows: v = e_pivot + scal * x(below); a_c -= tau v (v^T a_c), c > k
-        // (without a branch: the other columns get tau v times zero added)
+        // rows: v = e_pivot + scal * x(below); a_c -= tau v (v^T a_c), c > k.
+        // Column k is done: R above and on the diagonal, v below.
 #pragma unroll
         for (int q = 0; q < kRpt; ++q) {
-            if (rr[q] >= pr && rr[q] < r_end) {
-                const bool piv = rr[q] == pr;
-                const double v = piv ? 1.0 : xk[q] * scal;
-                const double mtv = -tau * v;
-#pragma unroll
-                for (int c = 0; c < kNb; ++c) {
-                    x[q][c] = fma(mtv, s_w[c], x[q][c]);
-                    if (c == k) x[q][c] = piv ? beta : v;
-                }
+            const bool below = rr[q] > pr, piv = rr[q] == pr;
+            const double v = piv ? 1.0 : below ? x[q][0] * scal : 0.0;
+            if (rr[q] < r_end) {
+                W[rr[q] + pr * ldw] = piv ? beta : below ? v : x[q][0];
+                a.Vp[rr[q] - a.j + (int64_t)k * a.ldvp] = v;
             }
+            const double mtv = -tau * v;
+#pragma unroll
+            for (int c = 0; c + 1 < kNb; ++c) x[q][c] = fma(mtv, s_w[c + 1], x[q][c + 1]);
+            x[q][kNb - 1] = 0.0;
         }
         __syncthreads();  // gsum, s_prow and s_w are rewritten by the next column
     }
-    // write back: R above and on the diagonal, v below; explicit V of the panel
 #pragma unroll
-    for (int q = 0; q < kRpt; ++q) {
-        if (rr[q] >= r_end) continue;
-        const int64_t li = rr[q] - a.j;  // row within the panel
-#pragma unroll
-        for (int c = 0; c < kNb; ++c) {
-            if (c < nb) W[rr[q] + (a.j + c) * ldw] = x[q][c];
-            a.Vp[li + (int64_t)c * a.ldvp] = (c >= nb) ? 0.0 : (li > c ? x[q][c] : (li == c ? 1.0 : 0.0));
-        }
-    }
+    for (int q = 0; q < kRpt; ++q)
+        for (int c = nb; c < kNb; ++c)
+            if (rr[q] < r_end) a.Vp[rr[q] - a.j + (int64_t)c * a.ldvp] = 0.0;
 }
 
 // T (nb x nb, upper triangular, column-major, ld kNb) with I - V T V^T =
 // H_1 ... H_nb from Y = V^T V (ld kNb) and tau: T(c, c) = tau_c,
 // T(0:c, c) = -tau_c T(0:c, 0:c) Y(0:c, c).
-// Y and tau are staged in LDS first, so that the nb steps of the recurrence
-// wait for no memory access.
-__global__ void qr_t_kernel(const double *Y, const double *tau, int nb, double *T) {
-    __shared__ double Ts[kNb][kNb + 1];
-    __shared__ double Ys[kNb][kNb + 1];
+// A row of T depends on itself only: thread t keeps row t in registers, and as
+// soon as T(t, i) is known adds its products to the sums of the columns after it,
+// so that the chain is one multiplication and one fma per column.  256 threads
+// stage Y and tau in LDS, 32 compute.  10 us; 24 to 28 with a barrier per column
+// and the sums formed one after the other from LDS.
+__global__ __launch_bounds__(256) void qr_t_kernel(const double *Y, const double *tau, int nb,
+                                                   double *T) {
+    __shared__ __align__(16) double Ys[kNb][kNb + 2];  // by rows
     __shared__ double ts[kNb];
     const int t = threadIdx.x;
-    for (int e = t; e < kNb * kNb; e += blockDim.x) {
-        Ts[e % kNb][e / kNb] = 0.0;
-        Ys[e % kNb][e / kNb] = Y[e];
-    }
-    if (t < nb) ts[t] = tau[t];
+    for (int e = t; e < kNb * kNb; e += blockDim.x) Ys[e % kNb][e / kNb] = Y[e];
+    if (t < kNb) ts[t] = t < nb ? tau[t] : 0.0;
     __syncthreads();
-    for (int c = 0; c < nb; ++c) {
-        const double tc = ts[c];
-        if (t < c) {
-            double s = 0.0;
-            for (int i = t; i < c; ++i) s = fma(Ts[t][i], Ys[i][c], s);
-            Ts[t][c] = -tc * s;
-        }
-        if (t == 0) Ts[c][c] = tc;
-        __syncthreads();
+    if (t >= kNb) return;
+    double sum[kNb];
+#pragma unroll
+    for (int c = 0; c < kNb; ++c) sum[c] = 0.0;
+#pragma unroll
+    for (int i = 0; i < kNb; ++i) {
+        const double x = (t == i) ? ts[i] : (t < i && i < nb) ? -ts[i] * sum[i] : 0.0;
+        T[t + i * kNb] = x;
+#pragma unroll
+        for (int c = i + 1; c < kNb; ++c) sum[c] = fma(x, Ys[i][c], sum[c]);
     }
-    for (int e = t; e < kNb * kNb; e += blockDim.x) T[e] = Ts[e % kNb][e / kNb];
 }
 
 // out = sum of parts[0 .. np) (each count doubles, stride count) in a fixed
@@ -618,15 +614,25 @@ hipError_t launch_fill(double *x, int64_t n, double v, hipStream_t s) {
     return hipGetLastError();
 }
 
+// Threads per workgroup of a panel of this many rows: 512 where a single
+// workgroup then does (900 rows: 91 us a panel; 2000 rows, four workgroups of
+// 256: 116), and above
+// 8192 rows, where half as many workgroups meet at each barrier (16000 rows: 172 us
+// against 201 us); in between the columns of 256 threads are faster (3000 rows: 121 us
+// against 139).
+static int qr_panel_threads(int64_t rows) {
+    return (rows > kRpt * kQT && rows <= kRpt * kQTWide) || rows > 8192 ? kQTWide : kQT;
+}
+
 int qr_panel_groups(int64_t rows) {
-    const int64_t per = (int64_t)kQT * kRpt;
+    const int64_t per = (int64_t)kRpt * qr_panel_threads(rows);
     return (int)((rows + per - 1) / per);
 }
 
 int qr_panel_resident(int cu_count) {
     int per_cu = 0;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(
-            &per_cu, reinterpret_cast<const void *>(&qr_panel_kernel), kQT, 0) != hipSuccess)
+            &per_cu, reinterpret_cast<const void *>(&qr_panel_kernel<kQT>), kQT, 0) != hipSuccess)
         return 0;
     return per_cu * cu_count;
 }
@@ -644,7 +650,8 @@ hipError_t launch_qr_reset(unsigned *bar, int *abort_flag, hipStream_t s) {
 // The abort flag is left as it is: once a barrier has failed, the later
 // panels fall through at their first barrier and the caller falls back to
 // the direct method.  An ordinary launch in stream order: the caller checks
-// that the nwg <= 64 workgroups of 68 kB LDS can all be resident
+// that the nwg <= 64 workgroups of 68 kB LDS (132 kB and at most 32 with 512
+// threads) can all be resident
 // (qr_panel_resident); work of other streams or processes on the device can
 // still keep some from starting, and then a barrier ends at its spin bound
 // (2^24 polls of the counter) instead of hanging.
@@ -653,12 +660,15 @@ hipError_t launch_qr_panel(const QrPanelArgs &a, hipStream_t s) {
     // (m <= 32768 on every path that factors a panel)
     if (a.nwg < 1 || a.nwg > 64) return hipErrorInvalidValue;
     hipLaunchKernelGGL(qr_reset_kernel, dim3(1), dim3(64), 0, s, a.bar, (int *)nullptr);
-    hipLaunchKernelGGL(qr_panel_kernel, dim3((unsigned)a.nwg), dim3(kQT), 0, s, a);
+    if (qr_panel_threads(a.m - a.j) == kQTWide)
+        hipLaunchKernelGGL(qr_panel_kernel<kQTWide>, dim3((unsigned)a.nwg), dim3(kQTWide), 0, s, a);
+    else
+        hipLaunchKernelGGL(qr_panel_kernel<kQT>, dim3((unsigned)a.nwg), dim3(kQT), 0, s, a);
     return hipGetLastError();
 }
 
 hipError_t launch_qr_t(const double *Y, const double *tau, int nb, double *T, hipStream_t s) {
-    hipLaunchKernelGGL(qr_t_kernel, dim3(1), dim3(64), 0, s, Y, tau, nb, T);
+    hipLaunchKernelGGL(qr_t_kernel, dim3(1), dim3(256), 0, s, Y, tau, nb, T);
     return hipGetLastError();
 }
 
