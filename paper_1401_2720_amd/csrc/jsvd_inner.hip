@@ -512,12 +512,14 @@ __global__ __launch_bounds__(InnerCfg<BW>::kThreads) void inner_kernel(StepArgs 
 // Appl. 13, 1992), and G and V only ever see the product V' of the rotations.
 // It takes no Cholesky factorization and no dot products: a pair's h_pp, h_qq
 // and h_pq are entries of H.  Launch without a V stream, n = 4096, 2w = 64:
-// 48.6 us (on R: 82); n = 1000 x 777, 2w = 32: 18.3 us (33.5).  It is bound by
-// the chain of BW - 1 dependent steps, about 1100 cycles each at 2w = 32, of
-// which 520 for the LDS reads and the rotation's some 45 dependent FP64
-// operations (10 cycles each), 390 to publish it and 150 at the barrier; at
-// 2w = 64 about 1600, where the four SIMDs' instruction issue fills the step
-// as well.  What is on that chain is one wave's work:
+// 48.5 us (on R: 82); n = 1024, 2w = 32: 17.6 us (33.5).  It is bound by
+// the chain of BW - 1 dependent steps, about 1050 cycles each at 2w = 32, of
+// which some 560 for the LDS reads and the rotation's some 48 dependent FP64
+// operations (10 cycles each), 300 to publish it and 150 at the barrier (where
+// the pair's entry lies in H is in the table: with the swaps followed by address
+// arithmetic in the chain, 18.3 us); at 2w = 64 about 1600, where the LDS is busy
+// for half of the step and the reads and writes of all waves come in turn.  What
+// is on that chain is one wave's work:
 //
 //   wave 0      (rotations) one lane per pivot pair.  While the other waves
 //               apply step s, it forms the entry h_pq of its pair of step
@@ -615,7 +617,7 @@ __device__ __forceinline__ void pair_gram32(const StepArgs &a, int2 pq, double *
 // SOLVE: one workgroup does the whole solve of a single pivot pair (n <= 32,
 // w = 16), G and V in global memory (cache): per sweep the Gram matrix, this
 // kernel's inner sweeps and the updates of G and V, then the singular values,
-// U and the order.  Bound by the chain of the inner sweep (17 us of about 20
+// U and the order.  Bound by the chain of the inner sweep (16 us of about 20
 // per sweep); four launches, a copy and a wait per sweep take 58 us.
 template <int BW, bool HYP, bool SOLVE = false>
 __global__ __launch_bounds__(JacCfg<BW>::kThreads) void jacobi_kernel(StepArgs a) {
@@ -625,15 +627,16 @@ __global__ __launch_bounds__(JacCfg<BW>::kThreads) void jacobi_kernel(StepArgs a
     constexpr int EPT = BW * BW / NT;   // Gram entries summed per thread
     constexpr int HB = BW * LD * 8;     // bytes of one buffer of H
     // H, columns of V' on their way (xch, by slot), position_tables' entry of
-    // every step and pair, and of them what the V waves take (vctl); or the
-    // four V' of two p-steps' V updates at once
+    // every step and pair and where wave 0 finds the pair's entry of H (tbl), and
+    // of them what the V waves take (vctl); or the four V' of two p-steps' V
+    // updates at once
     constexpr int kH = 2 * BW * LD, kXch = 2 * NP * BW, kTbl = NS * NP;
-    constexpr int kArena = kH + kXch + kTbl + (kTbl + 1) / 2;
+    constexpr int kArena = kH + kXch + 2 * kTbl + (kTbl + 1) / 2;
     __shared__ __align__(16) double arena[BW == 64 && kArena < 4 * BW * BW ? 4 * BW * BW : kArena];
     double(*const H)[BW * LD] = reinterpret_cast<double(*)[BW * LD]>(arena);
     double(*const xch)[NP * BW] = reinterpret_cast<double(*)[NP * BW]>(arena + kH);
-    uint2 *const tbl = reinterpret_cast<uint2 *>(arena + kH + kXch);
-    unsigned *const vctl = reinterpret_cast<unsigned *>(arena + kH + kXch + kTbl);
+    uint4 *const tbl = reinterpret_cast<uint4 *>(arena + kH + kXch);
+    unsigned *const vctl = reinterpret_cast<unsigned *>(arena + kH + kXch + 2 * kTbl);
     __shared__ double diag[BW];              // h_cc by position
     __shared__ double2 prm[2][NP];           // published rotations: tan, cos (swapped: -cos)
     __shared__ double mtn[2][HYP ? NP : 1];  // -t tan (hyperbolic pairs: + tan)
@@ -737,10 +740,18 @@ __global__ __launch_bounds__(JacCfg<BW>::kThreads) void jacobi_kernel(StepArgs a
     }
     if (table_due && 2 * tid < NS * NP) {
         auto put = [&](int e, unsigned lo, unsigned hi) {
-            tbl[e] = make_uint2(lo, hi);
             // where the sent column goes (bytes in xch); bit 31: the kept
             // column is y; bit 30: it is kept again
             vctl[e] = (hi >> 24) * (BW * 8) | (hi & 0x20000u) << 14 | (hi & 0x40000u) << 12;
+            // Before the step, the two columns were rotated in pairs I and J of
+            // the step before.  Offsets in H of that block's entries (0, 0),
+            // (0, 1) and (1, 0); (1, 1) is (0, 0) moved by NP both ways.  I, J,
+            // and in bits 31 and 30 whether x (y) was the second of its pair.
+            const unsigned I = (lo & 0xff) % NP, J = ((lo >> 8) & 0xff) % NP;
+            tbl[e] = make_uint4(
+                lo, hi, (min(I, J) * LD + max(I, J)) * 8 | (I * LD + J + NP) * 8 << 16,
+                (J * LD + I + NP) * 8 | I << 16 | J << 21 |
+                    ((lo & 0xff) >= NP ? 0x80000000u : 0) | (((lo >> 8) & 0xff) >= NP ? 0x40000000u : 0));
         };
         put(2 * tid, tv.x, tv.y);
         put(2 * tid + 1, tv.z, tv.w);
@@ -838,13 +849,7 @@ __global__ __launch_bounds__(JacCfg<BW>::kThreads) void jacobi_kernel(StepArgs a
     int rot_total = 0, proper_total = 0, clamp_total = 0, sweeps = 0, rot_sweep = 0;
     double off = 0.0;           // h_pq after the pair's rotation,
     unsigned off_at = 0;        // and where it goes
-    uint2 tn0 = tbl[k], tn1{};  // the table entries of the coming two steps
-    // The next step's two columns were rotated in pairs Ia and Jb of this one,
-    // into the columns now at positions r and c; fa, fb: whether they sit in
-    // the second place of their pair.  Offsets in H of their entry before the
-    // rotations, h00, and of those it takes in (of the pair partners' entries).
-    unsigned h00 = 0, h01 = 0, h10 = 0, h11 = 0, Ia = 0, Jb = 0;
-    bool fa = false, fb = false;
+    uint4 tn = tbl[k];          // the table entry of the coming step
     // V waves: slots 4 vw .. 4 vw + 3, BW/2 lanes per slot, two rows per lane.
     // vk: the column of V' kept from the step before; vr: the other one.
     constexpr int VS = Cfg::kVSlots;
@@ -853,9 +858,8 @@ __global__ __launch_bounds__(JacCfg<BW>::kThreads) void jacobi_kernel(StepArgs a
     unsigned ctl[VS];
 
     // decide and compute the rotation of pair k in the step of table entry t
-    // (h_pp, h_qq, h_pq given), publish it and the new diagonal; nxt: the
-    // next step's entry
-    auto rotate_pair = [&](uint2 t, uint2 nxt, int slot, double hpp, double hqq,
+    // (h_pp, h_qq, h_pq given), publish it and the new diagonal
+    auto rotate_pair = [&](uint4 t, int slot, double hpp, double hqq,
                            double hpq) __attribute__((always_inline)) {
         const int cp = t.y & 0xff, cq = (t.y >> 8) & 0xff;
         bool hyp = false;
@@ -869,7 +873,6 @@ __global__ __launch_bounds__(JacCfg<BW>::kThreads) void jacobi_kernel(StepArgs a
         const double up = __builtin_bit_cast(
             double, __builtin_bit_cast(unsigned long long, hqq - hpp) ^ ((unsigned long long)flip << 32));
         const bool swap = (up > 0.0) & (max(cp, cq) < cmax) & !(HYP && hyp);
-        const unsigned ms = (unsigned)__builtin_amdgcn_ballot_w64(swap);
         const unsigned dp8 = ((t.x >> 16) & 0xff) * 8, dq8 = (t.x >> 24) * 8;
         const unsigned np8 = swap ? dq8 : dp8, nq8 = swap ? dp8 : dq8;
 
@@ -905,21 +908,7 @@ __global__ __launch_bounds__(JacCfg<BW>::kThreads) void jacobi_kernel(StepArgs a
         dst[slot][k] = np8 | nq8 << 16;
         *reinterpret_cast<double *>(reinterpret_cast<char *>(diag) + np8) = npp;
         *reinterpret_cast<double *>(reinterpret_cast<char *>(diag) + nq8) = nqq;
-        // for the next step, while these stores are on their way (placed before the
-        // chain above, to fill its gaps, these instructions lengthen it)
         off_at = at(dp8, dq8);
-        const unsigned sp = nxt.x & 0xff, sq = (nxt.x >> 8) & 0xff;
-        Ia = sp % NP;
-        Jb = sq % NP;
-        const unsigned r8 = (sp ^ ((ms >> Ia) & 1u) * NP) * 8, c8 = (sq ^ ((ms >> Jb) & 1u) * NP) * 8;
-        const unsigned r8o = r8 ^ (NP * 8), c8o = c8 ^ (NP * 8);
-        fa = r8 >= NP * 8;
-        fb = c8 >= NP * 8;
-        h00 = at(r8, c8);
-        h01 = at(r8, c8o);
-        h10 = at(r8o, c8);
-        h11 = at(r8o, c8o);
-        asm volatile("" : "+v"(h00), "+v"(h01), "+v"(h10), "+v"(h11), "+v"(off_at));
     };
 
     // one step; PAR: its parity
@@ -930,18 +919,27 @@ __global__ __launch_bounds__(JacCfg<BW>::kThreads) void jacobi_kernel(StepArgs a
         auto put = [&](unsigned o, double v) { *reinterpret_cast<double *>(hn + o) = v; };
         if (on_rot) {
             if (st + 1 < NS) {
-                const double x00 = ld(h00), x01 = ld(h01), x10 = ld(h10), x11 = ld(h11);
-                const double2 ra = prm[PAR][Ia], rb = prm[PAR][Jb];
+                // the new pair's entry is that of two rotated columns of the
+                // pairs I and J: c_I c_J u^T X w with X the block before the
+                // rotations and u, w = (1, -tan) for a pair's first column,
+                // (tan, 1) for its second (the other one if it was swapped)
+                const uint4 t = tn;
+                const unsigned I = (t.w >> 16) & 31, J = (t.w >> 21) & 31;
+                const unsigned s00 = t.z & 0xffff;
+                const double2 ra = prm[PAR][I], rb = prm[PAR][J];
+                const double x00 = ld(s00), x01 = ld(t.z >> 16), x10 = ld(t.w & 0xffff),
+                             x11 = ld(s00 + (NP * LD + NP) * 8);
                 const double hpp = diag[k], hqq = diag[k + NP];
-                const double ma = HYP ? mtn[PAR][HYP ? Ia : 0] : -ra.x;
-                const double mb = HYP ? mtn[PAR][HYP ? Jb : 0] : -rb.x;
+                const double ma = HYP ? mtn[PAR][HYP ? I : 0] : -ra.x;
+                const double mb = HYP ? mtn[PAR][HYP ? J : 0] : -rb.x;
                 put(off_at, off);
-                const uint2 t = tn0;
-                tn0 = tn1;
-                tn1 = tbl[min(st + 3, NS - 1) * NP + k];
-                const double ga = fa ? ra.x : ma, gb = fb ? rb.x : mb;
-                const double x0 = fma(gb, x01, x00), x1 = fma(gb, x11, x10);
-                rotate_pair(t, tn0, 1 - PAR, hpp, hqq, fabs(ra.y * rb.y) * fma(ga, x1, x0));
+                tn = tbl[min(st + 2, NS - 1) * NP + k];
+                auto high = [](double v) { return (unsigned)(__builtin_bit_cast(unsigned long long, v) >> 32); };
+                const bool fa = (int)(high(ra.y) ^ t.w) < 0, fb = (int)(high(rb.y) ^ t.w << 1) < 0;
+                const double u0 = fa ? ra.x : 1.0, u1 = fa ? 1.0 : ma;
+                const double w0 = fb ? rb.x : 1.0, w1 = fb ? 1.0 : mb;
+                const double x0 = fma(w1, x01, w0 * x00), x1 = fma(w1, x11, w0 * x10);
+                rotate_pair(t, 1 - PAR, hpp, hqq, fabs(ra.y * rb.y) * fma(u1, x1, u0 * x0));
             } else {
                 put(off_at, off);
             }
@@ -1047,10 +1045,9 @@ __global__ __launch_bounds__(JacCfg<BW>::kThreads) void jacobi_kernel(StepArgs a
             for (int u = 0; u < VS; ++u) ctl[u] = vctl[vs + u];
         }
         if (on_rot) {
-            const uint2 t = tbl[k];
-            tn0 = tbl[NP + k];
-            tn1 = tbl[2 * NP + k];
-            rotate_pair(t, tn0, 0, diag[k], diag[k + NP], H[0][k * LD + k + NP]);
+            const uint4 t = tbl[k];
+            tn = tbl[NP + k];
+            rotate_pair(t, 0, diag[k], diag[k + NP], H[0][k * LD + k + NP]);
         }
         __syncthreads();
         for (int st = 0; st + 1 < NS; st += 2) {
