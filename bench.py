@@ -60,14 +60,14 @@ TIMING_STRIDE = 8
 def kernel_roofline(name, avg_ms, per_launch):
     """Roofline entry of one p-step kernel from its algorithmic work per
     launch: HBM- or MFMA-bound by its arithmetic intensity against the
-    ridge point; the inner kernel, whose Cholesky and Jacobi work is a chain
-    of dependent FP64 vector operations, against the FP64 vector peak."""
+    ridge point; the inner kernel, whose Jacobi work is a chain of dependent
+    FP64 vector operations, against the FP64 vector peak."""
     sec = avg_ms * 1e-3
     if name == "inner":
         # achieved: the inner Jacobi's algorithmic cost per launch, 36 w n^2
-        # s_in flops per block sweep over the nb - 1 launches of a sweep;
-        # achieved_actual: the same work counted from the run's rotations,
-        # inner sweeps and Cholesky factorizations
+        # s_in flops per block sweep over the nb - 1 launches of a sweep, for
+        # the one-sided method on the Cholesky factor; achieved_actual: what
+        # the kernel does instead, two-sided rotations of the Gram matrix
         achieved = per_launch["inner_flops_model"] / sec / 1e12
         actual = per_launch["inner_flops"] / sec / 1e12
         return {"kernel": "inner", "bound": "alu", "achieved": achieved,
@@ -571,25 +571,24 @@ def main():
     #           flops per pair on the m x bw columns (read once);
     #   update  [G_p G_q] V'_pq for the pairs with a transformation: 2 m bw^2
     #           flops, the columns read and written;
-    #   inner   Cholesky (bw^3 / 3), per inner step and pair the three dot
-    #           products (6 bw) and per rotation the update of two columns of
-    #           R and of V' (12 bw), FP64 vector work; the same launch also
-    #           streams the previous p-step's V update (2 n bw^2 flops, n x bw
-    #           columns read and written per transformed pair);
+    #   inner   per inner step the two-sided rotation of H's 2 x 2 blocks
+    #           (w^2 / 2 of them, 20 flops each) and the rotation of V' (w
+    #           pairs of columns, 6 bw flops each): 22 w^2, FP64 vector work;
+    #           the same launch also carries an earlier p-step's V update (2 n
+    #           bw^2 flops, n x bw columns read and written per transformed
+    #           pair, or half of that where two p-steps' go together);
     #   fused   the update of a p-step and the next p-step's Gram matrices in
     #           one launch: both kernels' flops, G read once and the
     #           transformed pairs' columns written.
     launches = sum(sweeps) * steps_per_sweep
     upd_per_launch = sum(updates) / max(launches, 1)
-    rot_per_launch = sum(rotations) / max(launches, 1)
     isw_per_launch = sum(inner_sweeps) / max(launches, 1)
     per_launch = {
         "gram_flops": npairs * float(bw) * (bw + 1) * m,
         "gram_bytes": npairs * m * bw * 8.0,
         "update_flops": upd_per_launch * 2.0 * m * bw * bw,
         "update_bytes": upd_per_launch * m * bw * 8.0 * 2,
-        "inner_flops": (isw_per_launch * (bw - 1) * (bw // 2) * 6.0 * bw
-                        + rot_per_launch * 12.0 * bw + npairs * bw ** 3 / 3.0),
+        "inner_flops": isw_per_launch * (bw - 1) * 22.0 * (bw // 2) ** 2,
         # the algorithmic model of the inner Jacobi: per block sweep about
         # n^2 / (2 w^2) pivot block-pairs, each inner sweep (2w - 1) w pivot
         # pairs at 6 (2w) flops for the dot products and 12 (2w) for rotating

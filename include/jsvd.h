@@ -8,9 +8,9 @@
  *   - block level (Section 2, eqs. (2.6)-(2.9); Section 4): the columns of
  *     G and V are split into block-columns of width w; a parallel pivot
  *     strategy (Section 3) pairs them; for each pair (p, q) the Gram matrix
- *     H_pq = [G_p G_q]^T [G_p G_q] is formed and Cholesky-factored, eq.
- *     (2.7), an inner Jacobi orthogonalises the 2w x 2w factor
- *     (Section 4.3), and the accumulated transformation V'_pq updates
+ *     H_pq = [G_p G_q]^T [G_p G_q] is formed, eq. (2.7), an inner Jacobi
+ *     (Section 4.3) diagonalises it by two-sided rotations (or, in the
+ *     scaled mode, orthogonalises its 2w x 2w Cholesky factor), and the accumulated transformation V'_pq updates
  *     [G_p G_q] and [V_p V_q], eq. (2.9);
  *   - a block sweep repeats until it performs no proper rotation
  *     (Section 4.5).
@@ -273,9 +273,9 @@ int jsvd_hsvd(jsvd_handle_t h, int64_t m, int64_t n, double *A, int64_t lda,
  * method, Section 2 eqs. (2.3)-(2.5) with the rotations (4.3)-(4.6), in the
  * p-steps of the closest parallel strategy of Section 3: pointwise for the
  * smaller problems, and for those with n >= jsvd_batched_block_min_n(h) the
- * two-level method with block-columns of 16 (Gram matrix (2.7), Cholesky,
- * one inner sweep on R, update (2.9))), in two persistent launches (the
- * blocked problems, then the others): workgroups pull problems from a device
+ * two-level method with block-columns of 16 (Gram matrix (2.7), one inner
+ * sweep on it, update (2.9))), in up to three persistent launches (the
+ * blocked problems, those that one wave solves, the others): workgroups pull problems from a device
  * queue, largest n first, and each runs its problem to its own convergence (a
  * sweep with no proper rotation, Section 4.5) or opts->max_sweeps.
  *   batch        : number of problems (0 is allowed: nothing is done).
@@ -457,7 +457,7 @@ int32_t jsvd_batched_block_min_n(jsvd_handle_t h);
 /*
  * Measurement aid: per-kernel GPU time of the block sweeps, taken with HIP
  * events recorded on the handle's stream around every launch of the
- * p-step kernels (index 0 = Gram, 1 = inner Cholesky and Jacobi, 2 =
+ * p-step kernels (index 0 = Gram, 1 = inner Jacobi, 2 =
  * update, 3 = the update fused with the next p-step's Gram kernel).  jsvd_kernel_timing(h, k) with k > 0 turns it on for every k-th
  * p-step of each sweep (k = 1: all; a larger k keeps the events' own cost
  * out of the run) and zeroes the totals; (h, 0) turns it off.
@@ -481,8 +481,8 @@ int jsvd_diag_fp64(jsvd_handle_t h, int64_t count, const double *a, const double
                    double *quot, double *root);
 
 /*
- * Diagnostic: the refined FP64 operations that the inner rotations (4.3)-(4.6)
- * and the Cholesky pivots of Section 4.1 use in place of IEEE division and
+ * Diagnostic: the refined FP64 operations that the rotations of columns
+ * (4.3)-(4.6) and the Cholesky pivots of Section 4.1 use in place of IEEE division and
  * square root, evaluated on the device by the very functions of the kernels,
  * for count operand pairs (a[i], b[i]):
  *   out[0 count + i] = reciprocal of b[i]     (Newton-refined hardware seed)

@@ -37,7 +37,12 @@ KERNEL_SOURCES = {"gram": ["jsvd_gram.hip"],
                   "inner": ["jsvd_inner.hip", "jsvd_rows.h", "jsvd_blocked.h", "jsvd_qrpair.h"],
                   "update": ["jsvd_update.hip", "jsvd_rows.h"],
                   "fused": ["jsvd_fused.hip"]}
-PSTEP = re.compile(r"\b(gram|inner|update|fused)_kernel<(\d+)(?:, (?:true|false))*>")
+PSTEP = re.compile(r"\b(gram|inner|jacobi|update|fused)_kernel<(\d+)(?:, (?:true|false))*>")
+
+
+def _pstep_name(m):
+    """inner_kernel<2w> for either inner kernel."""
+    return f"{m.group(1).replace('jacobi', 'inner')}_kernel<{m.group(2)}>"
 
 
 def kernel_sources_sha256(kernel):
@@ -58,7 +63,7 @@ def _counter_means(path, calib_kernel):
         value = float(row["Counter_Value"])
         m = PSTEP.search(name)
         if m:
-            per[f"{m.group(1)}_kernel<{m.group(2)}>"].append(value)
+            per[_pstep_name(m)].append(value)
         elif calib_kernel in name:
             calib.append(value)
     return per, calib
@@ -116,13 +121,13 @@ def mfma(counter_csv, stats_csv, simds=1024, clock_ghz=2.4, peak_tflops=78.6):
     for row in csv.DictReader(open(counter_csv)):
         m = PSTEP.search(row["Kernel_Name"])
         if m:
-            per[f"{m.group(1)}_kernel<{m.group(2)}>"][row["Counter_Name"]].append(
+            per[_pstep_name(m)][row["Counter_Name"]].append(
                 float(row["Counter_Value"]))
     avg_us = {}
     for row in csv.DictReader(open(stats_csv)):
         m = PSTEP.search(row["Name"])
         if m:
-            avg_us[f"{m.group(1)}_kernel<{m.group(2)}>"] = float(row["AverageNs"]) / 1e3
+            avg_us[_pstep_name(m)] = float(row["AverageNs"]) / 1e3
     print("| kernel | FP64 MFMA FLOP per launch (mean / max) | MFMA busy cycles per SIMD (mean) | "
           "average duration (us) | achieved TFLOP/s | of 78.6 peak | MFMA pipe busy |")
     print("|---|---|---|---|---|---|---|")
