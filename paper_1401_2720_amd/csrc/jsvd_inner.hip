@@ -512,14 +512,14 @@ __global__ __launch_bounds__(InnerCfg<BW>::kThreads) void inner_kernel(StepArgs 
 // Appl. 13, 1992), and G and V only ever see the product V' of the rotations.
 // It takes no Cholesky factorization and no dot products: a pair's h_pp, h_qq
 // and h_pq are entries of H.  Launch without a V stream, n = 4096, 2w = 64:
-// 48.5 us (on R: 82); n = 1024, 2w = 32: 17.6 us (33.5).  It is bound by
+// 44.8 us (on R: 82); n = 1024, 2w = 32: 17.6 us (33.5).  It is bound by
 // the chain of BW - 1 dependent steps, about 1050 cycles each at 2w = 32, of
 // which some 560 for the LDS reads and the rotation's some 48 dependent FP64
 // operations (10 cycles each), 300 to publish it and 150 at the barrier (where
 // the pair's entry lies in H is in the table: with the swaps followed by address
-// arithmetic in the chain, 18.3 us); at 2w = 64 about 1600, where the LDS is busy
-// for half of the step and the reads and writes of all waves come in turn.  What
-// is on that chain is one wave's work:
+// arithmetic in the chain, 18.3 us); at 2w = 64 about 1480, where three SIMDs issue
+// some 300 vector instructions per step for the H and V waves and the LDS is busy
+// for half of it.  What is on that chain is one wave's work:
 //
 //   wave 0      (rotations) one lane per pivot pair.  While the other waves
 //               apply step s, it forms the entry h_pq of its pair of step
@@ -530,7 +530,8 @@ __global__ __launch_bounds__(InnerCfg<BW>::kThreads) void inner_kernel(StepArgs 
 //               BW = 64): block read, rotated from both sides, written to
 //               where step s + 1 has its columns;
 //   V waves     V' <- V' J, four slots (pairs) per wave, a lane holding two
-//               rows of its slots' columns in registers.  From step to step a
+//               rows (four at BW = 64: two slots of two rows took 48.5 us) of its
+//               slot's columns in registers.  From step to step a
 //               slot keeps one column and passes the other one on through LDS
 //               (position_tables).
 //
@@ -548,7 +549,7 @@ struct JacCfg {
     static constexpr int kSteps = BW - 1;
     static constexpr int kLD = BW + 1;
     static constexpr int kBlocks = BW / 32;       // 2 x 2 blocks per lane of an H wave
-    static constexpr int kVSlots = BW / 32;       // slots per lane of a V wave
+    static constexpr int kVRows = BW / 32;        // pairs of rows per lane of a V wave
     // roles by wave.  Waves go to the four SIMDs round robin; wave 0's SIMD
     // gets little other work.
     static constexpr int kHFirst = 1, kHCount = BW == 64 ? 4 : 2, kVCount = BW / 8;
@@ -850,12 +851,13 @@ __global__ __launch_bounds__(JacCfg<BW>::kThreads) void jacobi_kernel(StepArgs a
     double off = 0.0;           // h_pq after the pair's rotation,
     unsigned off_at = 0;        // and where it goes
     uint4 tn = tbl[k];          // the table entry of the coming step
-    // V waves: slots 4 vw .. 4 vw + 3, BW/2 lanes per slot, two rows per lane.
-    // vk: the column of V' kept from the step before; vr: the other one.
-    constexpr int VS = Cfg::kVSlots;
-    const int vs = 4 * (vw < 0 ? 0 : vw) + (lane / NP) * VS, vrow = 2 * (lane % NP);
-    double2 vk[VS], vr[VS];
-    unsigned ctl[VS];
+    // V waves: slots 4 vw .. 4 vw + 3, 16 lanes per slot, the rows 2 l, 2 l + 1 (and
+    // 32 further) in lane l.  vk: the column of V' kept from the step before; vr:
+    // the other one.
+    constexpr int VR = Cfg::kVRows;
+    const int vs = 4 * (vw < 0 ? 0 : vw) + lane / 16, vrow = 2 * (lane % 16);
+    double2 vk[VR], vr[VR];
+    unsigned ctl = 0;
 
     // decide and compute the rotation of pair k in the step of table entry t
     // (h_pp, h_qq, h_pq given), publish it and the new diagonal
@@ -975,36 +977,36 @@ __global__ __launch_bounds__(JacCfg<BW>::kThreads) void jacobi_kernel(StepArgs a
                 put(at(A1, B1), cc * fma(ri[b].x, y0, y1));
             }
         } else if (vw >= 0) {
-            double2 r[VS];
-            double m[VS];
+            if (st > 0)
 #pragma unroll
-            for (int u = 0; u < VS; ++u) {
-                if (st > 0) vr[u] = *reinterpret_cast<const double2 *>(&xch[1 - PAR][(vs + u) * BW + vrow]);
-                r[u] = prm[PAR][vs + u];
-                m[u] = HYP ? mtn[PAR][HYP ? vs + u : 0] : 0.0;
+                for (int u = 0; u < VR; ++u)
+                    vr[u] = *reinterpret_cast<const double2 *>(&xch[1 - PAR][vs * BW + vrow + 32 * u]);
+            const double2 r = prm[PAR][vs];
+            const double m = HYP ? mtn[PAR][HYP ? vs : 0] : 0.0;
+            // tan as seen from the kept column
+            const unsigned long long mask = (unsigned long long)(ctl & 0x80000000u) << 32;
+            double tk = __builtin_bit_cast(double, __builtin_bit_cast(unsigned long long, r.x) ^ mask);
+            double mk = -tk;
+            if (HYP) {
+                tk = mask ? m : r.x;
+                mk = mask ? r.x : m;
             }
+            const double c = fabs(r.y);
+            // swapped columns are each other's
+            const bool same = ((ctl & 0x40000000u) != 0) != (r.y < 0.0);
 #pragma unroll
-            for (int u = 0; u < VS; ++u) {
-                // tan as seen from the kept column
-                const unsigned long long mask = (unsigned long long)(ctl[u] & 0x80000000u) << 32;
-                double tk = __builtin_bit_cast(double, __builtin_bit_cast(unsigned long long, r[u].x) ^ mask);
-                double mk = -tk;
-                if (HYP) {
-                    tk = mask ? m[u] : r[u].x;
-                    mk = mask ? r[u].x : m[u];
-                }
-                const double c = fabs(r[u].y);
+            for (int u = 0; u < VR; ++u) {
                 const double2 k1 = make_double2(c * fma(mk, vr[u].x, vk[u].x), c * fma(mk, vr[u].y, vk[u].y));
                 const double2 r1 = make_double2(c * fma(tk, vk[u].x, vr[u].x), c * fma(tk, vk[u].y, vr[u].y));
-                // swapped columns are each other's
-                const bool same = ((ctl[u] & 0x40000000u) != 0) != (r[u].y < 0.0);
                 vk[u] = make_double2(same ? k1.x : r1.x, same ? k1.y : r1.y);
                 vr[u] = make_double2(same ? r1.x : k1.x, same ? r1.y : k1.y);
-                if (st + 1 < NS) {
-                    *reinterpret_cast<double2 *>(reinterpret_cast<char *>(&xch[PAR][vrow]) +
-                                                 (ctl[u] & 0xffff)) = vr[u];
-                    ctl[u] = vctl[(st + 1) * NP + vs + u];
-                }
+            }
+            if (st + 1 < NS) {
+#pragma unroll
+                for (int u = 0; u < VR; ++u)
+                    *reinterpret_cast<double2 *>(reinterpret_cast<char *>(&xch[PAR][vrow + 32 * u]) +
+                                                 (ctl & 0xffff)) = vr[u];
+                ctl = vctl[(st + 1) * NP + vs];
             }
         }
         __syncthreads();
@@ -1019,31 +1021,29 @@ __global__ __launch_bounds__(JacCfg<BW>::kThreads) void jacobi_kernel(StepArgs a
     };
     // the V waves' columns after the last step, to a column-major BW x BW matrix
     auto put_v = [&](double *out) __attribute__((always_inline)) {
+        int ck, cr;
+        kept_col((NS - 1) * NP + vs, ck, cr);
 #pragma unroll
-        for (int u = 0; u < VS; ++u) {
-            int ck, cr;
-            kept_col((NS - 1) * NP + vs + u, ck, cr);
-            *reinterpret_cast<double2 *>(out + ck * BW + vrow) = vk[u];
-            *reinterpret_cast<double2 *>(out + cr * BW + vrow) = vr[u];
+        for (int u = 0; u < VR; ++u) {
+            *reinterpret_cast<double2 *>(out + ck * BW + vrow + 32 * u) = vk[u];
+            *reinterpret_cast<double2 *>(out + cr * BW + vrow + 32 * u) = vr[u];
         }
     };
 
     if (on_rot) __builtin_amdgcn_s_setprio(3);
     if (vw >= 0) {  // V' = I
+        int ck, cr;
+        kept_col(vs, ck, cr);
 #pragma unroll
-        for (int u = 0; u < VS; ++u) {
-            int ck, cr;
-            kept_col(vs + u, ck, cr);
-            vk[u] = make_double2(vrow == ck ? 1.0 : 0.0, vrow + 1 == ck ? 1.0 : 0.0);
-            vr[u] = make_double2(vrow == cr ? 1.0 : 0.0, vrow + 1 == cr ? 1.0 : 0.0);
+        for (int u = 0; u < VR; ++u) {
+            const int i = vrow + 32 * u;
+            vk[u] = make_double2(i == ck ? 1.0 : 0.0, i + 1 == ck ? 1.0 : 0.0);
+            vr[u] = make_double2(i == cr ? 1.0 : 0.0, i + 1 == cr ? 1.0 : 0.0);
         }
     }
     for (int sw = 0; sw < a.max_inner_sweeps; ++sw) {
         rot_sweep = 0;
-        if (vw >= 0) {
-#pragma unroll
-            for (int u = 0; u < VS; ++u) ctl[u] = vctl[vs + u];
-        }
+        if (vw >= 0) ctl = vctl[vs];
         if (on_rot) {
             const uint4 t = tbl[k];
             tn = tbl[NP + k];
@@ -1068,12 +1068,12 @@ __global__ __launch_bounds__(JacCfg<BW>::kThreads) void jacobi_kernel(StepArgs a
             if (vw >= 0) put_v(all);
             __syncthreads();
             if (vw >= 0) {
+                int ck, cr;
+                kept_col(vs, ck, cr);
 #pragma unroll
-                for (int u = 0; u < VS; ++u) {
-                    int ck, cr;
-                    kept_col(vs + u, ck, cr);
-                    vk[u] = *reinterpret_cast<const double2 *>(all + ck * BW + vrow);
-                    vr[u] = *reinterpret_cast<const double2 *>(all + cr * BW + vrow);
+                for (int u = 0; u < VR; ++u) {
+                    vk[u] = *reinterpret_cast<const double2 *>(all + ck * BW + vrow + 32 * u);
+                    vr[u] = *reinterpret_cast<const double2 *>(all + cr * BW + vrow + 32 * u);
                 }
             }
             __syncthreads();
