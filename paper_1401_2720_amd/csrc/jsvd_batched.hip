@@ -394,7 +394,7 @@ __device__ __forceinline__ void finish_problem(const BatchArgs &b, int id, int m
 // and DRDSSQ norms.
 template <bool DD>
 __global__ __launch_bounds__(kBatchThreads) void batched_kernel(BatchArgs b) {
-    extern __shared__ double lds_g[];  // working copy of G when it fits
+    extern __shared__ __align__(16) double lds_g[];  // working copy of G when it fits
     __shared__ int s_item;
     __shared__ int s_rot;
     __shared__ int s_bad;
@@ -654,7 +654,7 @@ __device__ __forceinline__ void wave_problem(const BatchArgs &b, int id, int m, 
 // Problems at positions [queue[4], count) of the work order.
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4)))
 void batched_wave_kernel(BatchArgs b) {
-    extern __shared__ double lds_g[];  // G, then V
+    extern __shared__ __align__(16) double lds_g[];  // G, then V
     __shared__ double sig[kWaveMaxN];
     __shared__ int perm[kWaveMaxN];
     const int lane = threadIdx.x;
@@ -687,7 +687,7 @@ void batched_wave_kernel(BatchArgs b) {
 // pointwise method's.
 __global__ __launch_bounds__(kBlkThreads) __attribute__((amdgpu_waves_per_eu(4)))
 void batched_blocked_kernel(BatchArgs b) {
-    extern __shared__ double lds_g[];  // R, V' and the Gram reduction of the pivot pairs
+    extern __shared__ __align__(16) double lds_g[];  // BlkLds, with 16-byte accesses
     __shared__ int s_item;
     __shared__ double s_sig[kBatchMaxN];
     __shared__ int s_perm[kBatchMaxN];
