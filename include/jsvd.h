@@ -455,6 +455,15 @@ int32_t jsvd_strategy_order(int32_t nb);
 int32_t jsvd_batched_block_min_n(jsvd_handle_t h);
 
 /*
+ * The kernels that a batched call with these bounds launches on the handle, its
+ * tuning included: a sum of 1 (the blocked method), 2 (one wave per problem) and 4
+ * (the pointwise method in a workgroup per problem).  Only opts->want_v and
+ * opts->scaled are used.  Host only; a negative result is an argument index.
+ */
+int32_t jsvd_batched_kernels(jsvd_handle_t h, int64_t batch, int32_t max_m, int32_t max_n,
+                             const jsvd_opts *opts);
+
+/*
  * Measurement aid: per-kernel GPU time of the block sweeps, taken with HIP
  * events recorded on the handle's stream around every launch of the
  * p-step kernels (index 0 = Gram, 1 = inner Jacobi, 2 =

@@ -60,7 +60,7 @@ EXPORTS = ["jsvd_default_opts", "jsvd_create", "jsvd_set_stream", "jsvd_destroy"
            "jsvd_strategy_order",
            "jsvd_error_string",
            "jsvd_diag_fp64", "jsvd_kernel_timing", "jsvd_kernel_times", "jsvd_gesvd_batched",
-           "jsvd_svd_backward", "jsvd_set_tuning", "jsvd_batched_block_min_n",
+           "jsvd_svd_backward", "jsvd_set_tuning", "jsvd_batched_block_min_n", "jsvd_batched_kernels",
            "jsvd_workspace_size", "jsvd_workspace_size_batched", "jsvd_reserve_batched",
            "jsvd_diag_refined", "jsvd_gesvd_batched_noalloc", "jsvd_gesvd_full",
            "jsvd_colnorms", "jsvd_rdssq_bounds"]
@@ -92,6 +92,8 @@ def lib():
     L.jsvd_strategy_order.restype = _i32
     L.jsvd_batched_block_min_n.argtypes = [_vp]
     L.jsvd_batched_block_min_n.restype = _i32
+    L.jsvd_batched_kernels.argtypes = [_vp, _i64, _i32, _i32, ctypes.POINTER(Opts)]
+    L.jsvd_batched_kernels.restype = _i32
     L.jsvd_error_string.argtypes = [ctypes.c_int]
     L.jsvd_error_string.restype = ctypes.c_char_p
     L.jsvd_diag_fp64.argtypes = [_vp, _i64, _vp, _vp, _vp, _vp]
@@ -373,6 +375,20 @@ def batched_block_min_n(device_index=None):
     dev = torch.cuda.current_device() if device_index is None else device_index
     h = _handle(dev, torch.cuda.current_stream(dev).cuda_stream)
     return int(lib().jsvd_batched_block_min_n(h))
+
+
+def batched_kernels(batch, device_index=None, scaled="auto"):
+    """The kernels that gesvd_batched launches for a Batch: a set of "blocked",
+    "wave" (one wave per problem) and "pointwise"."""
+    import torch
+    dev = torch.cuda.current_device() if device_index is None else device_index
+    h = _handle(dev, torch.cuda.current_stream(dev).cuda_stream)
+    o = make_opts(want_v=batch.want_v, scaled=scaled)
+    rc = int(lib().jsvd_batched_kernels(h, batch.count, batch.max_m, batch.max_n,
+                                        ctypes.byref(o)))
+    if rc < 0:
+        raise JsvdError(rc, "jsvd_batched_kernels")
+    return {name for i, name in enumerate(("blocked", "wave", "pointwise")) if rc & (1 << i)}
 
 
 def diag_fp64(a, b):

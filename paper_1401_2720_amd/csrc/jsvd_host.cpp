@@ -1647,6 +1647,36 @@ int check_batched_args(jsvd_handle_t h, int64_t batch, int32_t max_m, int32_t ma
     return JSVD_OK;
 }
 
+// Which problems go to which kernel of a batched call.
+struct BatchRoute {
+    int blk_min_n, ddrjac, wave_lds, all_wave;  // as in BatchArgs
+};
+
+BatchRoute batch_route(const jsvd_handle_s *h, int64_t batch, int32_t max_m, int32_t max_n,
+                       const jsvd_opts &o) {
+    BatchRoute r{};
+    const int mn = h->tuning.batch_block_min_n ? h->tuning.batch_block_min_n : kBatchBlockMinN;
+    const bool room = h->batch_lds / (int64_t)sizeof(double) >= kBatchBlockLds;
+    r.blk_min_n = (room && mn <= kBatchMaxN) ? mn : 0;
+    // opts.scaled = 2: DDRJAC pairs and DRDSSQ norms, every problem pointwise
+    r.ddrjac = o.scaled == 2 ? 1 : 0;
+    if (r.ddrjac) r.blk_min_n = 0;
+    // one wave per small problem, with LDS for the largest that the bounds
+    // allow, up to kWaveMaxLds (smaller bounds, more waves on a CU).  Where
+    // every n <= kWaveMaxN fits it takes the pointwise kernel's place (20000
+    // problems of 20 x 12: 5.9 -> 1.16 ms); where some do not, both run, one
+    // after the other, and the second launch's tail (0.8 ms: 4000 ragged problems
+    // 13.6 -> 14.4 ms) is worth it only in a large batch.
+    const int64_t wn = std::min<int64_t>(max_n, kWaveMaxN);
+    const int64_t want = (int64_t)max_m * wn + (o.want_v ? wn * wn : 0);
+    const bool fits = want <= kWaveMaxLds;
+    r.wave_lds = !r.ddrjac && (fits || batch >= kWaveMinBatch)
+                     ? (int)std::min<int64_t>(want, kWaveMaxLds) : 0;
+    r.all_wave = r.wave_lds && fits &&
+                 (max_n <= kWaveMaxN || (r.blk_min_n > 0 && r.blk_min_n <= kWaveMaxN + 1));
+    return r;
+}
+
 // Enqueue the batched solve with its workspace at ws (batch_plan(h,
 // batch).total bytes): the work-order kernels, then the two persistent
 // launches.  Allocates nothing.
@@ -1681,30 +1711,11 @@ int launch_batched_solve(jsvd_handle_s *h, int64_t batch, int32_t max_m, int32_t
     // of all columns at a time
     if (b.lds_doubles < kBatchMaxN) return JSVD_HIP_ERROR;
     b.g_groups = h->tuning.batch_g_groups ? h->tuning.batch_g_groups : 16;
-    {
-        const int mn = h->tuning.batch_block_min_n ? h->tuning.batch_block_min_n
-                                                   : kBatchBlockMinN;
-        const bool room = b.lds_doubles >= kBatchBlockLds;
-        b.blk_min_n = (room && mn <= kBatchMaxN) ? mn : 0;
-    }
-    // opts.scaled = 2: DDRJAC pairs and DRDSSQ norms, every problem pointwise
-    b.ddrjac = o.scaled == 2 ? 1 : 0;
-    if (b.ddrjac) b.blk_min_n = 0;
-    // one wave per small problem, with LDS for the largest that the bounds
-    // allow, up to kWaveMaxLds (smaller bounds, more waves on a CU).  Where
-    // every n <= kWaveMaxN fits it takes the pointwise kernel's place (20000
-    // problems of 20 x 12: 5.9 -> 1.16 ms); where some do not, both run, one
-    // after the other, and the second launch's tail (0.8 ms: 4000 ragged problems
-    // 13.6 -> 14.4 ms) is worth it only in a large batch.
-    {
-        const int64_t wn = std::min<int64_t>(max_n, kWaveMaxN);
-        const int64_t want = (int64_t)max_m * wn + (o.want_v ? wn * wn : 0);
-        const bool fits = want <= kWaveMaxLds;
-        b.wave_lds = !b.ddrjac && (fits || batch >= kWaveMinBatch)
-                         ? (int)std::min<int64_t>(want, kWaveMaxLds) : 0;
-        b.all_wave = b.wave_lds && fits &&
-                     (max_n <= kWaveMaxN || (b.blk_min_n > 0 && b.blk_min_n <= kWaveMaxN + 1));
-    }
+    const BatchRoute r = batch_route(h, batch, max_m, max_n, o);
+    b.blk_min_n = r.blk_min_n;
+    b.ddrjac = r.ddrjac;
+    b.wave_lds = r.wave_lds;
+    b.all_wave = r.all_wave;
     for (int lg = 0; lg < 32; ++lg) b.t_hi[lg] = b.ddrjac ? rdssq_t_hi(lg) : 0.0;
     HIP_TRY(launch_batched(b, bp.grid, bp.bgrid, bp.wgrid, max_n, reinterpret_cast<int *>(ws + bp.off_hist),
                            reinterpret_cast<int32_t *>(ws + bp.off_order), h->stream));
@@ -1754,6 +1765,18 @@ int jsvd_gesvd_batched_noalloc(jsvd_handle_t h, int64_t batch, int32_t max_m, in
     if (hipSetDevice(h->device) != hipSuccess) return JSVD_HIP_ERROR;
     return launch_batched_solve(h, batch, max_m, max_n, m, n, a_off, s_off, v_off, A, S, V, o, status,
                                 sweeps, static_cast<char *>(h->noalloc_scratch));
+}
+
+int32_t jsvd_batched_kernels(jsvd_handle_t h, int64_t batch, int32_t max_m, int32_t max_n,
+                             const jsvd_opts *opts) {
+    const jsvd_opts o = opts ? *opts : defaults();
+    const int rc = check_batched_sizes(h, batch, max_m, max_n);
+    if (rc) return rc;
+    if (o.scaled < 0 || o.scaled > 2) return -5;
+    if (batch == 0) return 0;
+    const BatchRoute r = batch_route(h, batch, max_m, max_n, o);
+    return (r.blk_min_n > 0 && max_n >= r.blk_min_n ? 1 : 0) | (r.wave_lds > 0 ? 2 : 0) |
+           (r.ddrjac || !r.all_wave ? 4 : 0);
 }
 
 int jsvd_svd_backward(jsvd_handle_t h, int64_t batch, int64_t m, int64_t n, const double *U,

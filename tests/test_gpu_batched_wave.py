@@ -1,0 +1,92 @@
+"""The batched path's one-wave kernel: every lane-group width (n up to 4, 8, 16,
+32), rows at the edges of what a lane keeps in registers and beyond, with V and
+without, zero, repeated and graded columns; and the three kernels of a large
+mixed batch side by side.  The library says which kernels take a batch; every
+problem occurs many times, so that the batch is large, all copies have to come
+out with the same bits, and the first is compared with the oracle.
+
+Tolerances: sigma within 1e-12 sigma + 1e-13 sigma_1, orthogonality and the
+reconstruction within 1e-13 n, as for the other parity tests.
+"""
+import numpy as np
+import pytest
+
+import oracle
+
+pytestmark = pytest.mark.gpu
+
+# largest n of the batch (a lane-group width), its (m, n)
+WIDTHS = {
+    4: [(1, 1), (31, 1), (700, 1), (2, 2), (33, 2), (3, 3), (63, 3), (4, 4), (64, 4), (65, 4),
+        (257, 4), (764, 4)],
+    8: [(5, 5), (32, 5), (33, 6), (7, 7), (64, 7), (8, 8), (65, 8), (128, 8), (129, 8), (300, 8),
+        (376, 8)],
+    16: [(9, 9), (32, 9), (33, 10), (13, 13), (16, 16), (64, 16), (65, 15), (65, 16), (130, 12),
+         (176, 16)],
+    32: [(17, 17), (32, 17), (33, 18), (20, 20), (25, 25), (31, 31), (32, 32), (33, 32), (64, 31),
+         (64, 32)],
+}
+NO_V = {32: [(65, 17), (65, 32), (79, 24), (96, 32)], 16: [(192, 16), (129, 11)],
+        8: [(384, 8)], 4: [(768, 4)]}
+COPIES = 250
+
+
+def _jsvd():
+    import torch
+    import paper_1401_2720_amd as jsvd
+    return torch, jsvd
+
+
+def _special(n):
+    """Zero, repeated, parallel and graded columns."""
+    g = np.random.default_rng(n)
+    m = n + 7
+    z = g.standard_normal((m, n))
+    z[:, ::2] = 0.0
+    graded = g.standard_normal((m, n)) * 10.0 ** -np.linspace(0, 12, n)
+    return [np.zeros((m, n)), z, np.repeat(g.standard_normal((m, 1)), n, axis=1),
+            np.outer(g.standard_normal(m), g.standard_normal(n)), graded]
+
+
+def _run(mats, want_v, kernels):
+    torch, jsvd = _jsvd()
+    from paper_1401_2720_amd import _binding as B
+    b = jsvd.Batch(mats * COPIES, want_v=want_v)
+    assert B.batched_kernels(b) == kernels
+    print(f"{b.count} problems, max_m {b.max_m}, max_n {b.max_n}", flush=True)
+    jsvd.gesvd_batched(b)
+    torch.cuda.synchronize()
+    assert int(b.status.abs().sum()) == 0
+    for x in (b.A, b.S, b.V) if want_v else (b.A, b.S):
+        x = x.view(COPIES, -1)
+        assert torch.equal(x, x[:1].expand_as(x))
+    for i, A in enumerate(mats):
+        n = A.shape[1]
+        U, S, V = b.results(i)
+        ref = oracle.gesvj(A)["S"]
+        assert np.all(np.abs(S - ref) <= 1e-12 * ref + 1e-13 * ref[0]), A.shape
+        U1 = U[:, S > 1e-10 * S[0]] if S[0] > 0 else U[:, :0]
+        assert np.max(np.abs(U1.T @ U1 - np.eye(U1.shape[1])), initial=0.0) <= 1e-13 * 40, A.shape
+        if want_v:
+            assert np.max(np.abs(V.T @ V - np.eye(n))) <= 1e-13 * n, A.shape
+            assert np.linalg.norm(A - (U * S) @ V.T) <= 1e-13 * n * np.linalg.norm(A), A.shape
+
+
+@pytest.mark.parametrize("want_v", [True, False])
+@pytest.mark.parametrize("width", list(WIDTHS))
+def test_every_lane_group_width(width, want_v):
+    g = np.random.default_rng(width)
+    sizes = WIDTHS[width] + ([] if want_v else NO_V[width])
+    mats = [g.standard_normal(s) for s in sizes] + _special(width)
+    _run(mats, want_v, {"wave"})
+
+
+@pytest.mark.parametrize("want_v", [True, False])
+def test_beside_the_other_kernels(want_v):
+    """Problems that fit a wave, that do not although n <= 32, and larger ones."""
+    g = np.random.default_rng(5)
+    sizes = [(1, 1), (70, 2), (33, 5), (8, 8), (17, 12), (65, 16), (33, 25), (32, 32), (64, 32),
+             (90, 24), (90, 25), (300, 7), (300, 20), (400, 31), (97, 32), (40, 33), (64, 48),
+             (120, 64)]
+    mats = [g.standard_normal(s) for s in sizes] + _special(6) + _special(21) + _special(33)
+    _run(mats, want_v, {"blocked", "wave", "pointwise"})
