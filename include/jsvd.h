@@ -457,7 +457,8 @@ int32_t jsvd_batched_block_min_n(jsvd_handle_t h);
 /*
  * The kernels that a batched call with these bounds launches on the handle, its
  * tuning included: a sum of 1 (the blocked method), 2 (one wave per problem) and 4
- * (the pointwise method in a workgroup per problem).  Only opts->want_v and
+ * (the pointwise method in a workgroup per problem); which of 2 and 4 a problem goes
+ * to that either could take may depend on the sizes of all.  Only opts->want_v and
  * opts->scaled are used.  Host only; a negative result is an argument index.
  */
 int32_t jsvd_batched_kernels(jsvd_handle_t h, int64_t batch, int32_t max_m, int32_t max_n,

@@ -718,14 +718,17 @@ void batched_blocked_kernel(BatchArgs b) {
 
 // Work order: problem indices by non-increasing n (counting sort), those for
 // the wave kernel after all others.  Buckets: n, or kBatchMaxN + 1 + n for the
-// wave kernel's.
+// wave kernel's, and where the sort has to decide after these one for each n of its
+// problems of more than wave_rows(n) rows.
 __device__ __forceinline__ bool wave_fits(int m, int n, int wave_lds, bool v) {
     return n <= kWaveMaxN && (int64_t)m * n + (v ? n * n : 0) <= wave_lds;
 }
 
 __device__ __forceinline__ int batch_bucket(const BatchArgs &b, int64_t i) {
     const int n = b.n[i];
-    return wave_fits(b.m[i], n, b.wave_lds, b.V != nullptr) ? kBatchMaxN + 1 + n : n;
+    const int m = b.m[i];
+    if (!wave_fits(m, n, b.wave_lds, b.V != nullptr)) return n;
+    return kBatchMaxN + 1 + n + (b.wave_few > 0 && m > wave_rows(n) ? kWaveMaxN + 1 : 0);
 }
 
 // Both passes count in LDS first and go to the global buckets once per
@@ -744,29 +747,54 @@ __global__ __launch_bounds__(kSortThreads) void batch_count_kernel(BatchArgs b, 
         if (h[v]) atomicAdd(&hist[v], h[v]);
 }
 
-__global__ void batch_scan_kernel(int *hist, int max_n, int blk_min_n, int *queue) {
-    // one thread: bucket start positions, largest n first; the problems with
-    // n >= blk_min_n (blk_min_n > 0) come first and go to the blocked kernel
-    if (threadIdx.x == 0 && blockIdx.x == 0) {
+// one thread: bucket start positions, largest n first; the problems with
+// n >= blk_min_n (blk_min_n > 0) come first and go to the blocked kernel.
+// wave_few > 0: problems that fit a wave go to the pointwise kernel instead if it
+// is done with them before one wave is with the largest of the longer ones, which
+// takes about twice as long there (n <= 8: hardly longer).  The pointwise
+// kernel's time for a problem goes about as n, and wave_few is 2 (1) problems per
+// CU: if the sum of all n is no more than wave_few times that one's.  (n 8..24, m
+// up to 88: 600 problems 367 us pointwise and 491 by waves, 1000 549 and 505; 513 of
+// 100 x 20: 570 and 470.)
+// The counts are scanned in LDS (in global memory every bucket took 0.1 us).
+__global__ __launch_bounds__(kSortThreads) void batch_scan_kernel(int *hist, int max_n,
+                                                                  int blk_min_n, int wave_few,
+                                                                  int *queue) {
+    __shared__ int count[kBatchBuckets], start[kBatchBuckets];
+    for (int v = threadIdx.x; v < kBatchBuckets; v += kSortThreads) count[v] = start[v] = hist[v];
+    __syncthreads();
+    if (threadIdx.x == 0) {
         int pos = 0, nblk = 0;
+#pragma unroll 4
         for (int v = max_n; v >= 0; --v) {
-            const int c = hist[v];
-            hist[v] = pos;
-            pos += c;
+            start[v] = pos;
+            pos += count[v];
             if (blk_min_n > 0 && v >= blk_min_n) nblk = pos;
         }
         queue[0] = 0;     // next blocked problem
         queue[1] = nblk;  // next pointwise problem
         queue[2] = nblk;  // number of blocked problems
-        queue[4] = pos;   // number of problems before those
-        for (int v = kBatchBuckets - 1; v > kBatchMaxN; --v) {
-            const int c = hist[v];
-            hist[v] = pos;
-            pos += c;
+        int first = pos;  // of the wave kernel's
+        int64_t sum_n = 0;
+        int top = 0;
+        for (int longer = wave_few > 0 ? 1 : 0; longer >= 0; --longer) {
+            const int v0 = kBatchMaxN + 1 + longer * (kWaveMaxN + 1);
+#pragma unroll 11
+            for (int n = kWaveMaxN; n >= 0; --n) {
+                const int c = count[v0 + n];
+                start[v0 + n] = pos;
+                pos += c;
+                sum_n += (int64_t)c * n;
+                if (longer && c && top == 0) top = n;
+            }
         }
+        if (wave_few > 0 && sum_n <= (int64_t)wave_few * top) first = pos;
+        queue[4] = first;  // number of problems before the wave kernel's
         // the wave kernel's counters: queue c hands out every kWaveQueues-th one
-        for (int c = 0; c < kWaveQueues; ++c) queue[kWaveQueueAt + kWaveQueueGap * c] = queue[4] + c;
+        for (int c = 0; c < kWaveQueues; ++c) queue[kWaveQueueAt + kWaveQueueGap * c] = first + c;
     }
+    __syncthreads();
+    for (int v = threadIdx.x; v < kBatchBuckets; v += kSortThreads) hist[v] = start[v];
 }
 
 __global__ __launch_bounds__(kSortThreads) void batch_place_kernel(BatchArgs b, int *hist,
@@ -818,8 +846,8 @@ hipError_t launch_batched(const BatchArgs &b, int grid, int bgrid, int wgrid, in
     hipLaunchKernelGGL(batch_zero_kernel, dim3(1), dim3(256), 0, s, hist, kBatchBuckets);
     const unsigned blocks = (unsigned)((b.count + kSortItems - 1) / kSortItems);
     hipLaunchKernelGGL(batch_count_kernel, dim3(blocks), dim3(kSortThreads), 0, s, b, hist);
-    hipLaunchKernelGGL(batch_scan_kernel, dim3(1), dim3(64), 0, s, hist, max_n, b.blk_min_n,
-                       b.queue);
+    hipLaunchKernelGGL(batch_scan_kernel, dim3(1), dim3(kSortThreads), 0, s, hist, max_n, b.blk_min_n,
+                       b.wave_few, b.queue);
     hipLaunchKernelGGL(batch_place_kernel, dim3(blocks), dim3(kSortThreads), 0, s, b, hist, order);
     if (b.blk_min_n > 0 && max_n >= b.blk_min_n)
         hipLaunchKernelGGL(batched_blocked_kernel, dim3(bgrid), dim3(kBlkThreads),

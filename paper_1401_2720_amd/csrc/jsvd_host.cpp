@@ -1649,7 +1649,7 @@ int check_batched_args(jsvd_handle_t h, int64_t batch, int32_t max_m, int32_t ma
 
 // Which problems go to which kernel of a batched call.
 struct BatchRoute {
-    int blk_min_n, ddrjac, wave_lds, all_wave;  // as in BatchArgs
+    int blk_min_n, ddrjac, wave_lds, wave_few, all_wave;  // as in BatchArgs
 };
 
 BatchRoute batch_route(const jsvd_handle_s *h, int64_t batch, int32_t max_m, int32_t max_n,
@@ -1664,15 +1664,30 @@ BatchRoute batch_route(const jsvd_handle_s *h, int64_t batch, int32_t max_m, int
     // one wave per small problem, with LDS for the largest that the bounds
     // allow, up to kWaveMaxLds (smaller bounds, more waves on a CU).  Where
     // every n <= kWaveMaxN fits it takes the pointwise kernel's place (20000
-    // problems of 20 x 12: 5.9 -> 1.16 ms); where some do not, both run, one
-    // after the other, and the second launch's tail (0.8 ms: 4000 ragged problems
-    // 13.6 -> 14.4 ms) is worth it only in a large batch.
+    // problems of 20 x 12: 5.9 -> 0.61 ms).  Where some do not, both run, one
+    // after the other, and the second launch's tail pays in a large batch only
+    // (n 8..128: 4000 problems 14.6 ms with it and 13.6 without, 20000 63.5 and
+    // 64.4; n 2..40: 500 1.49 and 0.93, 8192 3.8 and 6.1).
     const int64_t wn = std::min<int64_t>(max_n, kWaveMaxN);
     const int64_t want = (int64_t)max_m * wn + (o.want_v ? wn * wn : 0);
-    const bool fits = want <= kWaveMaxLds;
+    // Few problems: the 16 waves of a workgroup are done with a problem before
+    // one wave is, if a lane has many more rows of a column than it keeps in
+    // registers (50 problems of 100 x 24: 285 us, one wave 554; 100 x 12: 111 and
+    // 155; 130 x 8: 84 and 91; 700 x 4: 79 and 87), or hardly fewer, and V's (64 x
+    // 32: 375 and 407; 56 x 28: 321 and 305).  Waves gain again once the
+    // workgroups take turns.  How often they do depends on all sizes, not only on
+    // the bounds, so from `few` problems to kWaveManyTurns times as many both
+    // kernels are launched (an empty launch: 6 us) and the sort decides
+    // (batch_scan_kernel).
+    const int64_t cus = h->cu_count;
+    const bool long_cols = max_m > wave_rows(max_n);
+    const int64_t few = long_cols ? (max_n <= 8 ? cus : 2 * cus)
+                        : max_n > 16 && o.want_v && max_m + max_n > kWaveRowsV ? cus : 0;
+    const bool fits = want <= kWaveMaxLds && batch > few;
     r.wave_lds = !r.ddrjac && (fits || batch >= kWaveMinBatch)
                      ? (int)std::min<int64_t>(want, kWaveMaxLds) : 0;
-    r.all_wave = r.wave_lds && fits &&
+    r.wave_few = r.wave_lds && fits && long_cols && batch <= kWaveManyTurns * few ? (int)few : 0;
+    r.all_wave = r.wave_lds && fits && !r.wave_few &&
                  (max_n <= kWaveMaxN || (r.blk_min_n > 0 && r.blk_min_n <= kWaveMaxN + 1));
     return r;
 }
@@ -1715,6 +1730,7 @@ int launch_batched_solve(jsvd_handle_s *h, int64_t batch, int32_t max_m, int32_t
     b.blk_min_n = r.blk_min_n;
     b.ddrjac = r.ddrjac;
     b.wave_lds = r.wave_lds;
+    b.wave_few = r.wave_few;
     b.all_wave = r.all_wave;
     for (int lg = 0; lg < 32; ++lg) b.t_hi[lg] = b.ddrjac ? rdssq_t_hi(lg) : 0.0;
     HIP_TRY(launch_batched(b, bp.grid, bp.bgrid, bp.wgrid, max_n, reinterpret_cast<int *>(ws + bp.off_hist),

@@ -156,11 +156,17 @@ constexpr int kBatchBlockMinN = 65;     // built-in: batched problems with n >= 
 constexpr int kBatchBlockLds = 9512;   // doubles of LDS the blocked method needs
 constexpr int kWaveMaxN = 32;           // largest n of a problem that one wave solves
 constexpr int kWaveMaxLds = 3072;       // doubles of LDS of such a wave, at most (64 x 32, and V)
+// Rows up to which one wave is done with a problem of n columns no later than the 16
+// waves of a workgroup (with V and n > 16: up to kWaveRowsV of G and V together),
+// and turns that the workgroups have to take, from which waves are used at any
+// number of rows.
+constexpr int wave_rows(int n) { return n <= 4 ? 512 : n <= 8 ? 96 : 64; }
+constexpr int kWaveRowsV = 84, kWaveManyTurns = 6;
 constexpr int kWaveMinBatch = 8192;     // batches of this size use the wave kernel beside the
                                         // pointwise one
 constexpr int kWaveQueues = 16, kWaveQueueAt = 64, kWaveQueueGap = 32;  // its counters (ints)
 constexpr int kBatchQueueInts = kWaveQueueAt + kWaveQueues * kWaveQueueGap;
-constexpr int kBatchBuckets = kBatchMaxN + 1 + kWaveMaxN + 1;  // of the work order's sort
+constexpr int kBatchBuckets = kBatchMaxN + 1 + 2 * (kWaveMaxN + 1);  // of the work order's sort
 constexpr int kBatchInnerOrder = 32;   // 2w of the blocked method's inner sweeps
 
 struct BatchArgs {
@@ -182,6 +188,7 @@ struct BatchArgs {
     int g_groups;                               // half waves rotating G when V is wanted (of 32)
     int blk_min_n;                              // problems with n >= this are blocked (0: none)
     int wave_lds;                               // doubles of LDS per problem of the wave kernel (0: none)
+    int wave_few;                               // > 0: the sort decides whether it takes any
     int all_wave;                               // every problem goes to the blocked or the wave kernel
     int ddrjac;                                 // 1: DDRJAC pairs and DRDSSQ norms (no blocked problems)
     double t_hi[32];                            // DRDSSQ upper bound by ceil(lg m)

@@ -90,3 +90,81 @@ def test_beside_the_other_kernels(want_v):
              (120, 64)]
     mats = [g.standard_normal(s) for s in sizes] + _special(6) + _special(21) + _special(33)
     _run(mats, want_v, {"blocked", "wave", "pointwise"})
+
+
+def _uniform(A, count, want_v, kernels):
+    torch, jsvd = _jsvd()
+    from paper_1401_2720_amd import _binding as B
+    b = jsvd.Batch.from_uniform(torch.from_numpy(A).cuda().expand(count, *A.shape), want_v=want_v)
+    assert B.batched_kernels(b) == kernels, count
+    assert B.batched_kernels(b, scaled="on") == {"pointwise"}
+    jsvd.gesvd_batched(b)
+    torch.cuda.synchronize()
+    assert int(b.status.abs().sum()) == 0
+    A, S = b.A.view(count, -1), b.S.view(count, -1)
+    assert torch.equal(S, S[:1].expand_as(S)) and torch.equal(A, A[:1].expand_as(A))
+    return A[0].cpu().numpy(), S[0].cpu().numpy()
+
+
+@pytest.mark.parametrize("m,n,want_v,turns", [
+    (64, 24, False, 0), (65, 24, False, 2), (96, 32, False, 2), (65, 9, True, 2), (64, 16, True, 0),
+    (97, 8, True, 1), (96, 8, True, 0), (513, 4, True, 1), (512, 4, True, 0), (52, 32, True, 0),
+    (53, 32, True, 1), (64, 20, True, 0), (64, 21, True, 1)])
+def test_few_problems_of_many_rows_stay_in_a_workgroup(m, n, want_v, turns):
+    """Up to `turns` problems per CU the pointwise kernel takes a batch of so many rows,
+    from there on the one-wave kernel does.  (For the longer columns the sort decides
+    up to six times as many problems: one more of equal size is enough.)"""
+    torch, _ = _jsvd()
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    A = np.random.default_rng(m + n).standard_normal((m, n))
+    ref = oracle.gesvj(A)["S"]
+    many = _uniform(A, 12 * cus + 1, want_v, {"wave"})
+    sort = turns and (m > 64 or n <= 8)
+    more = _uniform(A, turns * cus + 1, want_v, {"wave", "pointwise"} if sort else {"wave"})
+    assert np.array_equal(more[0], many[0]) and np.array_equal(more[1], many[1])
+    for _, S in [many] + ([_uniform(A, turns * cus, want_v, {"pointwise"})] if turns else []):
+        assert np.all(np.abs(S - ref) <= 1e-12 * ref + 1e-13 * ref[0])
+
+
+@pytest.mark.parametrize("m,n,turns", [(100, 24, 2), (300, 8, 1)])
+def test_the_sort_decides_by_all_sizes(m, n, turns):
+    """One long problem among small ones: pointwise until the sum of n exceeds
+    `turns` problems of that one's n per CU.  Which kernel had it shows in U's bits."""
+    torch, jsvd = _jsvd()
+    from paper_1401_2720_amd import _binding as B
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    A = np.random.default_rng(m * n).standard_normal((m, n))
+    by_wave = _uniform(A, 12 * cus + 1, True, {"wave"})[0]
+    by_workgroup = _uniform(A, cus, True, {"pointwise"})[0]
+    assert not np.array_equal(by_wave, by_workgroup)
+    room = turns * cus * n - n  # for the other problems' n, k of each but the last few
+    k = n // 4
+    for extra, want in ((0, by_workgroup), (1, by_wave)):
+        small = np.random.default_rng(1).standard_normal((k + 3, k))
+        ones = room % k + extra
+        b = jsvd.Batch([A] + [small] * (room // k) + [small[:, :1]] * ones)
+        assert turns * cus < b.count <= 6 * turns * cus
+        assert B.batched_kernels(b) == {"wave", "pointwise"}
+        jsvd.gesvd_batched(b)
+        torch.cuda.synchronize()
+        assert int(b.status.abs().sum()) == 0
+        assert np.array_equal(b.results(0)[0].ravel(order="F"), want), extra
+
+
+def test_the_sort_leaves_short_problems_to_waves():
+    """Bounds of more than 64 rows, but only a problem for the blocked kernel has them.
+    Which kernel had the first one shows in U's bits."""
+    torch, jsvd = _jsvd()
+    from paper_1401_2720_amd import _binding as B
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    g = np.random.default_rng(2)
+    A, big = g.standard_normal((60, 30)), g.standard_normal((90, 40))
+    by_wave = _uniform(A, 12 * cus + 1, False, {"wave"})[0]
+    b = jsvd.Batch([A, big] + [g.standard_normal((2, 1))] * (2 * cus), want_v=False)
+    assert B.batched_kernels(b) == {"blocked", "wave", "pointwise"}
+    jsvd.gesvd_batched(b)
+    torch.cuda.synchronize()
+    assert int(b.status.abs().sum()) == 0
+    assert np.array_equal(b.results(0)[0].ravel(order="F"), by_wave)
+    ref = oracle.gesvj(big)["S"]
+    assert np.all(np.abs(b.results(1)[1] - ref) <= 1e-12 * ref + 1e-13 * ref[0])
