@@ -366,9 +366,12 @@ hipError_t launch_gemm(const GemmArgs &g, hipStream_t s) {
     // 64 x 64 tiles where they give a workgroup per CU (256), 32 x 32 below
     // (more of the chip, each operand read twice as often).  The adjoint's five
     // products at 1024 x 1024 (256 tiles of 64): 0.27 ms with 64 x 64, 0.31 ms
-    // with 32 x 32; at 700 x 500 (88 tiles) 0.11 ms with 32 x 32.
+    // with 32 x 32; at 700 x 500 (88 tiles) 0.11 ms with 32 x 32.  Products of
+    // at most 32 rows or columns would fill half of a 64 x 64 tile: the adjoint of
+    // 2000 problems of 20 x 12 takes 53 us with 32 x 32, 95 with 64 x 64, of 400 of
+    // 64 x 32 46 and 54.
     const int64_t tiles = (int64_t)((g.M + 63) / 64) * ((g.N + 63) / 64) * g.batch;
-    if (tiles >= 256)
+    if (tiles >= 256 && g.M > 32 && g.N > 32)
         gemm_f64<2>(g, s);
     else
         gemm_f64<1>(g, s);

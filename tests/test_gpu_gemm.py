@@ -32,3 +32,37 @@ def test_adjoint_at_tile_edges(b, m, n):
     for i in range(b):
         want = adjoint.svd_adjoint(U[i], S[i], V[i], dU[i], dS[i], dV[i])
         assert np.linalg.norm(got[i] - want) <= tol * np.linalg.norm(want), i
+
+
+# products of at most 32 rows or columns beside larger ones, in batches of both tile sizes
+@pytest.mark.parametrize("b,m,n", [(300, 20, 12), (300, 32, 32), (300, 33, 32), (300, 33, 33),
+                                   (260, 64, 32), (260, 65, 33), (255, 32, 7)])
+def test_adjoint_of_many_small_problems(b, m, n):
+    test_adjoint_at_tile_edges(b, m, n)
+
+
+def test_small_products_do_not_pay_for_large_tiles():
+    """2000 adjoints of 20 x 12 against 249 of them (whose tiles are small either
+    way): 1.7 times the time with 32 x 32 tiles, 3.0 times with 64 x 64, which
+    would be a sixteenth full."""
+    import time
+    import torch
+    from paper_1401_2720_amd import _binding as B
+
+    def best(count, m=20, n=12):
+        g = torch.Generator("cuda").manual_seed(count)
+        r = lambda *s: torch.randn(*s, generator=g, dtype=torch.float64, device="cuda")
+        U, V, dU, dV, dS = r(count, n, m), r(count, n, n), r(count, n, m), r(count, n, n), r(count, n)
+        S = 2.0 - torch.arange(n, dtype=torch.float64, device="cuda") / n
+        S = S.expand(count, n).contiguous()
+        dA = torch.empty_like(U)
+        h = B._handle(0, torch.cuda.current_stream().cuda_stream)
+        args = [B._vp(x.data_ptr()) for x in (U, S, V, dU, dS, dV, dA)]
+        times = []
+        for _ in range(300):
+            t = time.perf_counter()
+            assert B.lib().jsvd_svd_backward(h, count, m, n, *args) == 0  # waits for the result
+            times.append(time.perf_counter() - t)
+        return min(times)
+
+    assert best(2000) < 2.3 * best(249)
