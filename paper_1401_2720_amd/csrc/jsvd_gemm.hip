@@ -87,7 +87,6 @@ __device__ __forceinline__ void gemm_stage(double *s,
 template <int WT, bool TA, bool TB>
 __global__ __launch_bounds__(kGemmThreads<32 * WT>) void gemm_f64_kernel(GemmArgs g) {
     constexpr int T = 32 * WT, LD = T + 2, KT = kGemmK;
-    constexpr int WY = 1;  // 16-column tiles per wave (WT 16-row ones)
     __shared__ __align__(16) double As[2][KT * LD];  // As[k][i] = op(A)[i0 + i][k0 + k]
     __shared__ __align__(16) double Bs[2][KT * LD];  // Bs[k][j] = op(B)[k0 + k][j0 + j]
     const int b = blockIdx.z;
@@ -111,11 +110,9 @@ __global__ __launch_bounds__(kGemmThreads<32 * WT>) void gemm_f64_kernel(GemmArg
     const int wi = (wave & 1) * 16 * WT, wj = (wave >> 1) * 16;
     const int l16 = lane & 15, lg = lane >> 4;
     const int ni = g.M - i0, nj = g.N - j0;
-    d4 acc[WT][WY];
+    d4 acc[WT];
 #pragma unroll
-    for (int x = 0; x < WT; ++x)
-#pragma unroll
-        for (int y = 0; y < WY; ++y) acc[x][y] = d4{0.0, 0.0, 0.0, 0.0};
+    for (int x = 0; x < WT; ++x) acc[x] = d4{0.0, 0.0, 0.0, 0.0};
 
     constexpr int NX = 2 * (16 * T / kGemmThreads<T>);
     auto load = [&](int k0, double (&xa)[NX], double (&xb)[NX]) __attribute__((always_inline)) {
@@ -133,15 +130,12 @@ __global__ __launch_bounds__(kGemmThreads<32 * WT>) void gemm_f64_kernel(GemmArg
         if (k0 + 2 * KT < kend) load(k0 + 2 * KT, ya, yb);
 #pragma unroll
         for (int kk = 0; kk < KT; kk += 4) {
-            double av[WT], bv[WY];
+            double av[WT];
 #pragma unroll
             for (int x = 0; x < WT; ++x) av[x] = As[buf][(kk + lg) * LD + wi + 16 * x + l16];
+            const double bv = Bs[buf][(kk + lg) * LD + wj + l16];
 #pragma unroll
-            for (int y = 0; y < WY; ++y) bv[y] = Bs[buf][(kk + lg) * LD + wj + 16 * y + l16];
-#pragma unroll
-            for (int x = 0; x < WT; ++x)
-#pragma unroll
-                for (int y = 0; y < WY; ++y) acc[x][y] = mfma16(bv[y], av[x], acc[x][y]);
+            for (int x = 0; x < WT; ++x) acc[x] = mfma16(bv, av[x], acc[x]);
         }
         if (k0 + KT < kend) stage(buf ^ 1, xa, xb);
         __syncthreads();
@@ -160,18 +154,16 @@ __global__ __launch_bounds__(kGemmThreads<32 * WT>) void gemm_f64_kernel(GemmArg
 #pragma unroll
     for (int x = 0; x < WT; ++x)
 #pragma unroll
-        for (int y = 0; y < WY; ++y)
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const int gi = i0 + wi + 16 * x + l16;
-                const int gj = j0 + wj + 16 * y + lg + 4 * v;
-                if (gi < g.M && gj < g.N) {
-                    double r = g.alpha == 1.0 ? acc[x][y][v] : g.alpha * acc[x][y][v];
-                    if (g.beta != 0.0) r = fma(g.beta, C[gi + (size_t)gj * g.ldc], r);
-                    if (g.E) r += g.E[(size_t)b * g.se + gi + (size_t)gj * g.lde] * g.d[(size_t)b * g.sd + gj];
-                    C[gi + (size_t)gj * g.ldc] = r;
-                }
+        for (int v = 0; v < 4; ++v) {
+            const int gi = i0 + wi + 16 * x + l16;
+            const int gj = j0 + wj + lg + 4 * v;
+            if (gi < g.M && gj < g.N) {
+                double r = g.alpha == 1.0 ? acc[x][v] : g.alpha * acc[x][v];
+                if (g.beta != 0.0) r = fma(g.beta, C[gi + (size_t)gj * g.ldc], r);
+                if (g.E) r += g.E[(size_t)b * g.se + gi + (size_t)gj * g.lde] * g.d[(size_t)b * g.sd + gj];
+                C[gi + (size_t)gj * g.ldc] = r;
             }
+        }
 }
 
 template <int WT>
