@@ -284,8 +284,13 @@ int choose_inner_sweeps(int64_t m, int64_t n) {
 // Block width and kernel tile shapes of a solve: w is the caller's, else
 // the handle's tuning table, else the built-in size rule; the shapes
 // (workgroups per Gram and update launch) come from the tuning entry of the
-// problem's size, else the built-in 256 (2048: 48.4 ms against 51.2 with 512)
-// and 1024.
+// problem's size if they were tuned for this w, else they are the built-in 256
+// (2048: 48.4 ms against 51.2 with 512) and 1024.  Where a caller asks for w = 16
+// at a size that the table or the rule gives w = 32, 256 leaves the narrower Gram
+// tiles too few rows in flight (per sweep with 256, 512 and 1024: n = 2000 6.0, 5.6
+// and 5.9 ms, 3000 19.3, 17.3 and 17.0; 1024 2.05, 2.10 and 2.10); and its updates
+// gain by 2048 (with 1024 and 2048: 1536 3.78 and 3.66 ms, 3000 17.3 and 17.1;
+// below 1100 no difference).
 struct Shapes {
     int w, gram_wg, update_wg;
 };
@@ -296,12 +301,14 @@ Shapes pick_shapes(const jsvd_handle_s *h, const jsvd_opts &o, int64_t m, int64_
         int i = 0;
         while (i + 1 < h->tuning.count && n > h->tuning.n_upper[i]) ++i;
         if (!sh.w) sh.w = h->tuning.block_w[i];
-        sh.gram_wg = h->tuning.gram_wg[i];
-        sh.update_wg = h->tuning.update_wg[i];
+        if (sh.w == h->tuning.block_w[i]) {
+            sh.gram_wg = h->tuning.gram_wg[i];
+            sh.update_wg = h->tuning.update_wg[i];
+        }
     }
     if (!sh.w) sh.w = choose_w(m, n);
-    if (!sh.gram_wg) sh.gram_wg = 256;
-    if (!sh.update_wg) sh.update_wg = 1024;
+    if (!sh.gram_wg) sh.gram_wg = sh.w == 16 && choose_w(m, n) > 16 ? 512 : 256;
+    if (!sh.update_wg) sh.update_wg = sh.w == 16 && n > 1024 ? 2048 : 1024;
     return sh;
 }
 

@@ -95,3 +95,17 @@ def test_batched_split_bitwise_equal(dev):
     for r in res[1:]:
         for x, y in zip(res[0], r):
             assert np.array_equal(x, y)
+
+
+def test_tile_shapes_belong_to_the_tuned_width(dev):
+    """A caller's block_w other than the entry's takes the built-in tile shapes: the
+    entry's were measured for another width (the Gram partial sums' workspace
+    follows the row splits)."""
+    from paper_1401_2720_amd import _binding as B
+    size = lambda w: B.workspace_size(700, 640, block_w=w)  # noqa: E731
+    B.set_tuning(dev, None)
+    built_in = {w: size(w) for w in (16, 32)}
+    for w, other in ((16, 32), (32, 16)):
+        B.set_tuning(dev, {"n_upper": [10 ** 6], "block_w": [w], "gram_wg": [64],
+                           "update_wg": [64]})
+        assert size(w) < built_in[w] and size(other) == built_in[other]
