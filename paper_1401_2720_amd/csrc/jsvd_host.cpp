@@ -358,11 +358,16 @@ struct Layout {
     size_t hpart, vprime, pair_rot, counters, perm, s_tmp, tmp, perm_in, rscratch, total;
 };
 
-// Slots of V'_pq: a p-step's is read by the next p-step's launch; where two
-// p-steps' V updates are done at once, by the three after it.
-int vprime_slots(int bw) { return bw == 64 ? 4 : 2; }
+// Whether V's updates of two p-steps may be done at once (if the ordering and the
+// input allow it), and the slots of V'_pq: a p-step's is read by the next p-step's
+// launch, then by the three after it.
+bool wants_v_pairs(const jsvd_opts &o, int64_t n, int w) {
+    return o.want_v && w == 32 && o.factorize != 1 && n >= 2560;
+}
 
-Layout plan(int64_t m, int64_t n, int bw, int npairs, int splits, bool hsvd) {
+int vprime_slots(bool v_pairs) { return v_pairs ? 4 : 2; }
+
+Layout plan(int64_t m, int64_t n, int bw, int npairs, int splits, bool hsvd, bool v_pairs) {
     Layout L;
     size_t off = 0;
     auto take = [&](size_t bytes) {
@@ -371,8 +376,8 @@ Layout plan(int64_t m, int64_t n, int bw, int npairs, int splits, bool hsvd) {
         return o;
     };
     L.hpart = take((size_t)npairs * splits * bw * bw * sizeof(double));
-    L.vprime = take((size_t)vprime_slots(bw) * npairs * bw * bw * sizeof(double));
-    L.pair_rot = take((size_t)vprime_slots(bw) * npairs * sizeof(int));
+    L.vprime = take((size_t)vprime_slots(v_pairs) * npairs * bw * bw * sizeof(double));
+    L.pair_rot = take((size_t)vprime_slots(v_pairs) * npairs * sizeof(int));
     L.counters = take(C_COUNT * sizeof(unsigned long long));
     L.perm = take((size_t)n * sizeof(int));
     L.s_tmp = take((size_t)n * sizeof(double));
@@ -525,7 +530,7 @@ int solve(jsvd_handle_s *h, int64_t m, int64_t n, double *A, int64_t lda, double
         if (r < 0) return -r;
         if (r == 1) {
             if (o.want_v && hsvd && perm_in_host) {
-                const Layout L = plan(m, n, 32, 1, 1, hsvd);
+                const Layout L = plan(m, n, 32, 1, 1, hsvd, false);
                 if ((rc = ensure_workspace(h, L.total))) return rc;
                 if ((rc = restore_rows(static_cast<char *>(h->ws), L))) return rc;
                 HIP_TRY(hipStreamSynchronize(st));
@@ -591,16 +596,15 @@ int solve(jsvd_handle_s *h, int64_t m, int64_t n, double *A, int64_t lda, double
     // below 2^32.
     const std::vector<int> *group_at = nullptr;
     const int *vquads = nullptr;
-    if (want_v && bw == 64 && w == 32 && !scaled && !qrf && n >= 2560 &&
-        ldv <= ((int64_t)1 << 26) &&
+    if (wants_v_pairs(o, n, w) && !scaled && ldv <= ((int64_t)1 << 26) &&
         (rc = get_step_groups(h, order, o.strategy, &group_at, &vquads)))
         return rc;
     const int lag = vquads ? 2 : 1;  // launches from a p-step to its V update
-    const int nslots = vprime_slots(bw);
+    const int nslots = vprime_slots(vquads != nullptr);
     const int64_t half_rows = align_up((size_t)((n + 1) / 2), 16);
     const int64_t quad_rows = quad_chunk_rows(half_rows, nquads, npairs, h->cu_count);
 
-    Layout L = plan(m, n, bw, npairs, splits, hsvd);
+    Layout L = plan(m, n, bw, npairs, splits, hsvd, vquads != nullptr);
     rc = ensure_workspace(h, L.total);
     if (rc) return rc;
     char *ws = static_cast<char *>(h->ws);
@@ -1945,7 +1949,7 @@ int jsvd_workspace_size(jsvd_handle_t h, int64_t m, int64_t n, const jsvd_opts *
     if (!bytes) return -5;
     // the Jacobi solve runs on G (m x n) or, after the QR preprocessing, on
     // R^T (n x n); the hyperbolic SVD adds the input column permutation
-    auto solve_bytes = [&](int64_t mm, int64_t nn, bool hsvd) {
+    auto solve_bytes = [&](const jsvd_opts &o, int64_t mm, int64_t nn, bool hsvd) {
         const Shapes shp = pick_shapes(h, o, mm, nn);
         auto bytes_at = [&](int w) {
             const int order = strategy_order((int)((nn + w - 1) / w));
@@ -1956,7 +1960,8 @@ int jsvd_workspace_size(jsvd_handle_t h, int64_t m, int64_t n, const jsvd_opts *
             for (int fused = 0; fused <= fuse_max; ++fused) {
                 const int tgt = split_target(h, o, shp, mm, order / 2, 2 * w, fused != 0);
                 const int splits = gram_splits(mm, order / 2, tgt, &rps);
-                bytes = std::max(bytes, plan(mm, nn, 2 * w, order / 2, splits, hsvd).total);
+                bytes = std::max(bytes, plan(mm, nn, 2 * w, order / 2, splits, hsvd,
+                                              wants_v_pairs(o, nn, w)).total);
             }
             return bytes;
         };
@@ -1964,8 +1969,12 @@ int jsvd_workspace_size(jsvd_handle_t h, int64_t m, int64_t n, const jsvd_opts *
         if (shp.w == 64) return hsvd ? bytes_at(32) : std::max(bytes_at(64), bytes_at(32));
         return bytes_at(shp.w);
     };
-    size_t total = std::max(solve_bytes(m, n, false), solve_bytes(m, n, true));
-    if (wants_qr(h, o, m, n)) total = std::max(total, solve_bytes(n, n, false)) + qr_plan(m, n).total;
+    size_t total = std::max(solve_bytes(o, m, n, false), solve_bytes(o, m, n, true));
+    if (wants_qr(h, o, m, n)) {
+        jsvd_opts oj = o;
+        oj.want_v = 1;  // R^T's V_x becomes U
+        total = std::max(total, solve_bytes(oj, n, n, false)) + qr_plan(m, n).total;
+    }
     if (o.scaled != 1) total += align_up((size_t)(n + 2) * sizeof(int), 256);
     *bytes = total;
     return JSVD_OK;

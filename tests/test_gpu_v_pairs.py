@@ -66,3 +66,16 @@ def test_hyperbolic():
     k = V.norm(2).item() ** 2
     assert (V.t() @ (Jd[:, None] * V) - torch.diag(Jt)).abs().max().item() <= 1e-13 * n * k
     assert (G @ V - U * S).norm().item() <= 1e-13 * n * k * G.norm().item()
+
+
+def test_workspace_holds_the_slots_in_use():
+    """Four slots of V' where two p-steps' V updates are done at once, else two."""
+    from paper_1401_2720_amd import _binding as B
+
+    def size(n, **opts):
+        return B.workspace_size(n, n, block_w=32, qr="off", **opts)
+
+    slot = B.strategy_order((3000 + 31) // 32) // 2 * 64 * 64 * 8
+    assert size(3000) - size(3000, want_v=False) >= 2 * slot
+    for n, opts in ((2048, {}), (2559, {}), (3000, {"factorize": "qr"})):
+        assert size(n, **opts) == size(n, want_v=False, **opts)
