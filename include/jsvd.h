@@ -446,6 +446,31 @@ int jsvd_inner_table(int32_t order, int32_t kind, int32_t *pairs);
  */
 int jsvd_quad_table(int32_t order, int32_t kind, int32_t *quads);
 
+/*
+ * Host only: the position table by which the inner kernels on the Gram matrix move
+ * its entries and the columns of V' (2w = order, 32 or 64; np = order / 2).  The pair
+ * in slot k of a p-step has its first column x at position k, its second, y, at np +
+ * k.  Per p-step and slot 8 bytes: the positions of x and y in the p-step before and
+ * in the next one (cyclically), x, y, flags, and the slot that the slot's sent column
+ * goes to; then the position of every column in p-step 0.  Flags: 1 if x > y; 2 if
+ * the column kept in the slot from the p-step before is y; 4 if that column is kept
+ * again (set in the last p-step).
+ *   table : host, (order - 1) * (order / 2) * 8 + order bytes.
+ * Returns JSVD_OK, -1 for another order, -2 for an unknown kind, -3 for NULL.
+ */
+int jsvd_position_table(int32_t order, int32_t kind, uint8_t *table);
+
+/*
+ * Host only: the p-steps of a table of jsvd_strategy_table taken two by two for V's
+ * updates, where a p-step and the next one form groups as in jsvd_quad_table.
+ *   at    : host, order - 1 int32: where in quads the groups of p-steps s and s + 1
+ *           start (the same for both), or -1 for a p-step that stays single.
+ *   quads : host, room for ((order - 1) / 2) * (order / 4) * 8 int32, filled from the
+ *           start: 8 per group as in jsvd_quad_table.
+ * Returns JSVD_OK, -1 for an unsupported order, -2 for an unknown kind, -3 for NULL.
+ */
+int jsvd_step_groups(int32_t order, int32_t kind, int32_t *at, int32_t *quads);
+
 /* Smallest supported strategy order >= max(nb, 2) (even, 2^k * o, o <= 11). */
 int32_t jsvd_strategy_order(int32_t nb);
 

@@ -57,6 +57,7 @@ class JsvdError(RuntimeError):
 _LIB = None
 EXPORTS = ["jsvd_default_opts", "jsvd_create", "jsvd_set_stream", "jsvd_destroy", "jsvd_gesvd",
            "jsvd_hsvd", "jsvd_strategy_table", "jsvd_inner_table", "jsvd_quad_table",
+           "jsvd_position_table", "jsvd_step_groups",
            "jsvd_strategy_order",
            "jsvd_error_string",
            "jsvd_diag_fp64", "jsvd_kernel_timing", "jsvd_kernel_times", "jsvd_gesvd_batched",
@@ -88,6 +89,8 @@ def lib():
     L.jsvd_strategy_table.argtypes = [_i32, _i32, _vp]
     L.jsvd_inner_table.argtypes = [_i32, _i32, _vp]
     L.jsvd_quad_table.argtypes = [_i32, _i32, _vp]
+    L.jsvd_position_table.argtypes = [_i32, _i32, _vp]
+    L.jsvd_step_groups.argtypes = [_i32, _i32, _vp, _vp]
     L.jsvd_strategy_order.argtypes = [_i32]
     L.jsvd_strategy_order.restype = _i32
     L.jsvd_batched_block_min_n.argtypes = [_vp]
@@ -363,6 +366,33 @@ def quad_table(order, kind="rrev"):
     if rc:
         raise JsvdError(rc, "jsvd_quad_table")
     return out.reshape(order - 2, order // 4, 8)
+
+
+def position_table(order, kind="rrev"):
+    """The inner kernels' position table for 2w = order (32 or 64): uint8 arrays
+    (order - 1, order / 2, 8) and (order,), the positions in p-step 0 (host only)."""
+    import numpy as np
+    steps = (order - 1) * (order // 2) * 8
+    out = np.zeros(steps + order, dtype=np.uint8)
+    k = STRATEGIES[kind] if isinstance(kind, str) else int(kind)
+    rc = lib().jsvd_position_table(int(order), k, _vp(out.ctypes.data))
+    if rc:
+        raise JsvdError(rc, "jsvd_position_table")
+    return out[:steps].reshape(order - 1, order // 2, 8), out[steps:]
+
+
+def step_groups(order, kind="rrev"):
+    """The p-steps two by two for V's updates: (at, quads), int32 arrays (order - 1,)
+    and (groups, 8); at[s] counts groups, -1 for a single p-step (host only)."""
+    import numpy as np
+    at = np.zeros(order - 1, dtype=np.int32)
+    quads = np.zeros(((order - 1) // 2) * (order // 4) * 8 + 1, dtype=np.int32)
+    k = STRATEGIES[kind] if isinstance(kind, str) else int(kind)
+    rc = lib().jsvd_step_groups(int(order), k, _vp(at.ctypes.data), _vp(quads.ctypes.data))
+    if rc:
+        raise JsvdError(rc, "jsvd_step_groups")
+    groups = int((at >= 0).sum()) // 2 * (order // 4)
+    return np.where(at >= 0, at // 8, -1), quads[:8 * groups].reshape(groups, 8)
 
 
 def strategy_order(nb):

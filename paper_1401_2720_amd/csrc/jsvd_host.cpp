@@ -1628,6 +1628,31 @@ int jsvd_quad_table(int32_t order, int32_t kind, int32_t *quads) {
     return JSVD_OK;
 }
 
+int jsvd_position_table(int32_t order, int32_t kind, uint8_t *table) {
+    if (kind < JSVD_STRAT_RREV || kind > JSVD_STRAT_RR) return -2;
+    if (!table) return -3;
+    Table t;
+    if ((order != 32 && order != 64) || !make_table(order, kind, t)) return -1;
+    order_for_banks(t);
+    std::vector<unsigned char> flat;
+    position_tables(t, flat);
+    std::copy(flat.begin(), flat.end(), table);
+    return JSVD_OK;
+}
+
+int jsvd_step_groups(int32_t order, int32_t kind, int32_t *at, int32_t *quads) {
+    if (kind < JSVD_STRAT_RREV || kind > JSVD_STRAT_RR) return -2;
+    if (!at || !quads) return -3;
+    if (order < 2 || order % 2 || strategy_order(order) != order || order > 4096) return -1;
+    Table t;
+    if (!make_table(order, kind, t)) return -1;
+    std::vector<int> starts, flat;
+    step_groups(t, starts, flat);
+    std::copy(starts.begin(), starts.end(), at);
+    std::copy(flat.begin(), flat.end(), quads);
+    return JSVD_OK;
+}
+
 int32_t jsvd_strategy_order(int32_t nb) { return strategy_order(nb); }
 
 int32_t jsvd_batched_block_min_n(jsvd_handle_t h) {
