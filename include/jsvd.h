@@ -537,6 +537,19 @@ int jsvd_diag_refined(jsvd_handle_t h, int64_t count, const double *a, const dou
                       double *out);
 
 /*
+ * Diagnostic: the rotation of the inner kernels on the Gram matrix and of the one-wave
+ * batched kernel (eqs. (4.3)-(4.6)), evaluated on the device by the kernels' own
+ * function, for count pairs of entries h_pp[i], h_qq[i], h_pq[i]:
+ *   out[0 count + i] = tan, out[1 count + i] = cos.
+ * hyperbolic: 0 for trigonometric pairs, 1 for hyperbolic ones.  All arrays are on the
+ * device; h_pp and h_qq are meant for [2^-450, 2^450], h_pq for what rotates there.
+ * Returns JSVD_OK, -1 if h is NULL, -2 for count < 0, -3 for a NULL array, -4 for
+ * another hyperbolic, or JSVD_HIP_ERROR.
+ */
+int jsvd_diag_rotation(jsvd_handle_t h, int64_t count, const double *hpp, const double *hqq,
+                       const double *hpq, int32_t hyperbolic, double *out);
+
+/*
  * DRDSSQ, the sum of squares of Appendix A, of every column of A: safe from
  * overflow and underflow over the whole double range, subnormals included.
  * For column c (m elements) with M = max |a_ic| and mu_c the smallest

@@ -63,7 +63,7 @@ EXPORTS = ["jsvd_default_opts", "jsvd_create", "jsvd_set_stream", "jsvd_destroy"
            "jsvd_diag_fp64", "jsvd_kernel_timing", "jsvd_kernel_times", "jsvd_gesvd_batched",
            "jsvd_svd_backward", "jsvd_set_tuning", "jsvd_batched_block_min_n", "jsvd_batched_kernels",
            "jsvd_workspace_size", "jsvd_workspace_size_batched", "jsvd_reserve_batched",
-           "jsvd_diag_refined", "jsvd_gesvd_batched_noalloc", "jsvd_gesvd_full",
+           "jsvd_diag_refined", "jsvd_diag_rotation", "jsvd_gesvd_batched_noalloc", "jsvd_gesvd_full",
            "jsvd_colnorms", "jsvd_rdssq_bounds"]
 
 
@@ -111,6 +111,7 @@ def lib():
                                               ctypes.POINTER(ctypes.c_size_t)]
     L.jsvd_reserve_batched.argtypes = [_vp, _i64, _i32, _i32, ctypes.POINTER(Opts)]
     L.jsvd_diag_refined.argtypes = [_vp, _i64, _vp, _vp, _vp]
+    L.jsvd_diag_rotation.argtypes = [_vp, _i64, _vp, _vp, _vp, _i32, _vp]
     L.jsvd_colnorms.argtypes = [_vp, _i64, _i64, _vp, _i64, _vp, _vp, _vp]
     L.jsvd_rdssq_bounds.argtypes = [_i32, ctypes.POINTER(ctypes.c_double),
                                     ctypes.POINTER(ctypes.c_double)]
@@ -120,7 +121,7 @@ def lib():
               "jsvd_gesvd", "jsvd_hsvd", "jsvd_strategy_table", "jsvd_diag_fp64",
               "jsvd_kernel_timing", "jsvd_kernel_times", "jsvd_gesvd_batched",
               "jsvd_svd_backward", "jsvd_workspace_size", "jsvd_workspace_size_batched",
-              "jsvd_reserve_batched", "jsvd_diag_refined", "jsvd_gesvd_batched_noalloc",
+              "jsvd_reserve_batched", "jsvd_diag_refined", "jsvd_diag_rotation", "jsvd_gesvd_batched_noalloc",
               "jsvd_gesvd_full", "jsvd_colnorms", "jsvd_rdssq_bounds"):
         getattr(L, f).restype = ctypes.c_int
     _LIB = L
@@ -483,6 +484,23 @@ def diag_refined(a, b):
     if rc:
         raise JsvdError(rc, "jsvd_diag_refined")
     return tuple(out.view(5, -1)[k] for k in range(5))
+
+
+def diag_rotation(hpp, hqq, hpq, hyperbolic=False):
+    """(tan, cos) of the rotation that zeroes h_pq, by the inner kernels' own device
+    function, for float64 CUDA tensors of entries of 2 x 2 Gram matrices."""
+    import torch
+    hpp, hqq, hpq = hpp.contiguous(), hqq.contiguous(), hpq.contiguous()
+    out = torch.empty(2 * hpp.numel(), dtype=torch.float64, device=hpp.device)
+    dev = hpp.device
+    h = _handle(dev.index if dev.index is not None else torch.cuda.current_device(),
+                torch.cuda.current_stream(dev).cuda_stream)
+    rc = lib().jsvd_diag_rotation(h, hpp.numel(), _vp(hpp.data_ptr()), _vp(hqq.data_ptr()),
+                                  _vp(hpq.data_ptr()), 1 if hyperbolic else 0,
+                                  _vp(out.data_ptr()))
+    if rc:
+        raise JsvdError(rc, "jsvd_diag_rotation")
+    return out[:hpp.numel()], out[hpp.numel():]
 
 
 def workspace_size(m, n, device_index=None, **opts):

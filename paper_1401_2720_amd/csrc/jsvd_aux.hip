@@ -158,6 +158,15 @@ __global__ void diag_refined_kernel(int64_t count, const double *a, const double
     }
 }
 
+__global__ void diag_rotation_kernel(int64_t count, const double *hpp, const double *hqq,
+                                     const double *hpq, bool hyp, double *out) {
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < count) {
+        bool clamped;
+        rotation_h(hpp[i], hqq[i], hpq[i], hyp, out[i], out[count + i], clamped);
+    }
+}
+
 }  // namespace
 
 hipError_t launch_reset_counters(unsigned long long *c, hipStream_t s) {
@@ -277,6 +286,13 @@ hipError_t launch_diag_refined(int64_t count, const double *a, const double *b, 
                                hipStream_t s) {
     hipLaunchKernelGGL(diag_refined_kernel, dim3((unsigned)((count + 255) / 256)), dim3(256), 0,
                        s, count, a, b, out);
+    return hipGetLastError();
+}
+
+hipError_t launch_diag_rotation(int64_t count, const double *hpp, const double *hqq,
+                                const double *hpq, bool hyp, double *out, hipStream_t s) {
+    hipLaunchKernelGGL(diag_rotation_kernel, dim3((unsigned)((count + 255) / 256)), dim3(256), 0,
+                       s, count, hpp, hqq, hpq, hyp, out);
     return hipGetLastError();
 }
 

@@ -237,7 +237,8 @@ __device__ __forceinline__ void rotation_fast(double hpp, double hqq, double hpq
 // (4.4) is |b| / (|d| + sqrt(d^2 + t b^2)), and cos = 1 / sqrt(1 + t tan^2).
 // What V' needs is that cos belongs to the double tan: cos is computed from
 // tan, with the rounding error of 1 + t tan^2 carried along, so that
-// cos^2 (1 + t tan^2) - 1 stays within 1.5 eps and averages zero (rotation:
+// cos^2 (1 + t tan^2) - 1 stays within 1.5 eps, for hyperbolic pairs (cos in [1, 2),
+// where rounding it once is worth 2) within 2 eps, and averages zero (rotation:
 // within 5 eps); tan itself is within 4 eps of the exact root, as
 // rotation's (averages 0.65 and 0.73 eps over random pairs).  Each
 // reciprocal and root is the hardware seed (relative error below 2^-22) and

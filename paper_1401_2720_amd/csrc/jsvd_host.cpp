@@ -1964,6 +1964,19 @@ int jsvd_diag_refined(jsvd_handle_t h, int64_t count, const double *a, const dou
     return JSVD_OK;
 }
 
+int jsvd_diag_rotation(jsvd_handle_t h, int64_t count, const double *hpp, const double *hqq,
+                       const double *hpq, int32_t hyperbolic, double *out) {
+    if (!h) return -1;
+    if (count < 0) return -2;
+    if (!hpp || !hqq || !hpq || !out) return -3;
+    if (hyperbolic != 0 && hyperbolic != 1) return -4;
+    if (count == 0) return JSVD_OK;
+    if (hipSetDevice(h->device) != hipSuccess) return JSVD_HIP_ERROR;
+    HIP_TRY(launch_diag_rotation(count, hpp, hqq, hpq, hyperbolic == 1, out, h->stream));
+    HIP_TRY(hipStreamSynchronize(h->stream));
+    return JSVD_OK;
+}
+
 int jsvd_workspace_size(jsvd_handle_t h, int64_t m, int64_t n, const jsvd_opts *opts,
                         size_t *bytes) {
     const jsvd_opts o = opts ? *opts : defaults();

@@ -312,5 +312,7 @@ hipError_t launch_diag_fp64(int64_t count, const double *a, const double *b, dou
                             double *r, hipStream_t s);
 hipError_t launch_diag_refined(int64_t count, const double *a, const double *b, double *out,
                                hipStream_t s);
+hipError_t launch_diag_rotation(int64_t count, const double *hpp, const double *hqq,
+                                const double *hpq, bool hyp, double *out, hipStream_t s);
 
 }  // namespace jsvd
