@@ -707,7 +707,7 @@ void batched_blocked_kernel(BatchArgs b) {
         if (V)
             for (int e = tid; e < n * n; e += kBlkThreads) V[e] = (e % n == e / n) ? 1.0 : 0.0;
         __syncthreads();
-        const int r = blocked_sweeps(G, V, m, n, min(b.max_sweeps, 0xffff), b.tbl_order,
+        const int r = blocked_sweeps(G, V, m, n, n, min(b.max_sweeps, 0xffff), b.tbl_order,
                                      b.tbl_off, b.tbls, b.jac, lds_g);
         const int status = (r & kBlkNonfinite) ? JSVD_NONFINITE
                            : (r & kBlkConverged) ? 0 : JSVD_NOT_CONVERGED;

@@ -387,13 +387,15 @@ __device__ __forceinline__ void blk_inner_sweep(BlkLds &L, const int *need, cons
 
 // The sweep loop of the blocked method on one problem (G: m x n, ld m; V:
 // n x n, ld n, identity on entry, or null).  lds holds kBlkLdsDoubles; jac:
-// position_tables' tables of order 32.
+// position_tables' tables of order 32.  Columns from n_real on are the caller's
+// padding, orthogonal to all others: they keep their places.
 // Returns the sweeps performed (max_sweeps <= 0xffff), plus kBlkConverged
 // when a sweep performed no proper rotation and kBlkNonfinite when a pivot
 // Gram matrix held a NaN or an infinity.  stats (LDS, three ints the caller
 // zeroes, or null) accumulates the rotations, the proper rotations and the
 // pivot pairs whose V' was applied.
-__device__ __forceinline__ int blocked_sweeps(double *G, double *V, int m, int n, int max_sweeps,
+__device__ __forceinline__ int blocked_sweeps(double *G, double *V, int m, int n, int n_real,
+                                              int max_sweeps,
                                               const int *tbl_order, const int64_t *tbl_off,
                                               const unsigned char *tbls, const unsigned char *jac,
                                               double *lds, int *stats = nullptr) {
@@ -535,8 +537,8 @@ __device__ __forceinline__ int blocked_sweeps(double *G, double *V, int m, int n
                             if (i == j) L.diag[wk][pi] = hs[t][v];
                         }
                     if (lane == 0) {
-                        const int nq = n - pq.y * kBlkW;
-                        s_cmax[wk] = nq > 0 ? kBlkW + min(kBlkW, nq) : min(kBlkW, n - pq.x * kBlkW);
+                        const int nq = n_real - pq.y * kBlkW;
+                        s_cmax[wk] = nq > 0 ? kBlkW + min(kBlkW, nq) : min(kBlkW, n_real - pq.x * kBlkW);
                     }
                 }
                 __syncthreads();

@@ -1369,7 +1369,11 @@ __global__ __launch_bounds__(kW128Threads) void inner128_kernel(StepArgs a) {
         Vg[e] = (i == j) ? 1.0 : 0.0;
     }
     __syncthreads();
-    const int r = blocked_sweeps(Rg, Vg, BW, BW, max(1, min(a.max_inner_sweeps, 0xffff)),
+    // the pair's padding columns are its last ones
+    const int64_t nq = a.n - (int64_t)pq.y * a.w;
+    const int n_real = (int)(nq > 0 ? a.w + min((int64_t)a.w, nq)
+                                    : min((int64_t)a.w, a.n - (int64_t)pq.x * a.w));
+    const int r = blocked_sweeps(Rg, Vg, BW, BW, n_real, max(1, min(a.max_inner_sweeps, 0xffff)),
                                  a.btbl_order, a.btbl_off, a.btbls, a.bjac, L, stats);
     __syncthreads();
     if (tid == 0) {
