@@ -147,7 +147,7 @@ def cpu_baseline(A, gpu_sweeps, target_s):
 
 def measure_batched(steps, warmup, cpu_seconds, plain_sample=200, scaled="auto"):
     """10,000 uneven problems (n ~ U{8..128}, m = n + U{0..64}, 20 % graded)
-    in the two persistent launches, captured in a HIP graph and replayed;
+    in its persistent launches, captured in a HIP graph and replayed;
     beside it the plain form (one jsvd_gesvd per problem, synchronising per
     sweep) on a fixed seeded sample of the same problems."""
     import numpy as np

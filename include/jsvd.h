@@ -10,8 +10,8 @@
  *     strategy (Section 3) pairs them; for each pair (p, q) the Gram matrix
  *     H_pq = [G_p G_q]^T [G_p G_q] is formed, eq. (2.7), an inner Jacobi
  *     (Section 4.3) diagonalises it by two-sided rotations (or, in the
- *     scaled mode, orthogonalises its 2w x 2w Cholesky factor), and the accumulated transformation V'_pq updates
- *     [G_p G_q] and [V_p V_q], eq. (2.9);
+ *     scaled mode, orthogonalises its 2w x 2w Cholesky factor), and the
+ *     accumulated transformation V'_pq updates [G_p G_q] and [V_p V_q], eq. (2.9);
  *   - a block sweep repeats until it performs no proper rotation
  *     (Section 4.5).
  *
@@ -289,7 +289,7 @@ int jsvd_hsvd(jsvd_handle_t h, int64_t m, int64_t n, double *A, int64_t lda,
  *                  n[i] x n[i], ldv = n[i].
  *   status       : device int32[batch] or NULL: 0 converged, JSVD_NOT_CONVERGED when
  *                  max_sweeps ended it, JSVD_NONFINITE when a blocked problem met a
- *                  NaN or infinite Cholesky pivot, or (opts->scaled = 2) a column
+ *                  NaN or an infinity in a pivot Gram matrix, or (opts->scaled = 2) a column
  *                  held a NaN or an infinity.
  *   sweeps       : device int32[batch] or NULL: sweeps performed.
  * Only opts->max_sweeps, opts->want_v and opts->scaled are used (block_w does
@@ -482,8 +482,8 @@ int32_t jsvd_batched_block_min_n(jsvd_handle_t h);
 /*
  * The kernels that a batched call with these bounds launches on the handle, its
  * tuning included: a sum of 1 (the blocked method), 2 (one wave per problem) and 4
- * (the pointwise method in a workgroup per problem); which of 2 and 4 a problem goes
- * to that either could take may depend on the sizes of all.  Only opts->want_v and
+ * (the pointwise method in a workgroup per problem).  With 2 and 4 both, which of them
+ * takes a problem may depend on the sizes of all.  Only opts->want_v and
  * opts->scaled are used.  Host only; a negative result is an argument index.
  */
 int32_t jsvd_batched_kernels(jsvd_handle_t h, int64_t batch, int32_t max_m, int32_t max_n,

@@ -1,4 +1,5 @@
-// Many independent small SVDs of uneven sizes in one persistent launch.
+// Many independent small SVDs of uneven sizes in a few persistent launches: one for
+// the blocked method, one with a wave per small problem, one with a workgroup each.
 //
 // The method is the same one-sided Jacobi as the dense path (Section 2,
 // eqs. (2.3)-(2.5); rotations (4.1), (4.3)-(4.6)), applied pointwise: a
@@ -457,9 +458,9 @@ __global__ __launch_bounds__(kBatchThreads) void batched_kernel(BatchArgs b) {
 // ------------------------------------------------------------ one wave each
 // Small problems (wave_fits: n <= 32 and G and V within wave_lds doubles): the
 // pointwise method with a whole problem in one wave and its LDS, so that a CU
-// works on up to 32 problems at once and no step waits for a barrier.  (One
+// works on up to 16 problems at once and no step waits for a barrier.  (One
 // 1024-thread workgroup per problem spends a step of a 20 x 12 problem on 12
-// of its 32 half waves and two barriers: 20000 of them took 5.9 ms.)  L lanes
+// of its 32 half waves and two barriers: 20000 of them took 5.9 ms, now 0.61.)  L lanes
 // per pivot pair, L the largest power of two with 64 / L >= pairs per step;
 // lane x owns rows x, x + L, ... of the pair's columns.  The steps, the test,
 // the rotations and the stopping rule are pointwise_sweeps'; the rotation is

@@ -425,7 +425,8 @@ int column_exponents(jsvd_handle_s *h, int64_t m, int64_t n, const double *A, in
 // (update_quad_rows, one workgroup per CU): the chunk of half_rows with which
 // the last workgroup ends first.  Measured per workgroup: 12 us to stage the
 // four V' and get going, and 7 us for every slice of 16 rows that a SIMD takes;
-// a CU that holds a pivot pair is free after 50 us.  At n = 4096 six chunks of
+// a CU that holds a pivot pair is free after 50 us (45 without the V stream beside
+// it; with 45 here n = 7424 takes 124 ms per sweep, with 50 122).  At n = 4096 six chunks of
 // 352 rows per quad (62 us per launch; eight of 256: 78 us), at 8192 four of
 // 1024 (194 us; sixteen of 256: 204 us, two of 2048: 280 us).
 int64_t quad_chunk_rows(int64_t half_rows, int nquads, int npairs, int cu) {
@@ -573,7 +574,8 @@ int solve(jsvd_handle_s *h, int64_t m, int64_t n, double *A, int64_t lda, double
     // Gram row splits (at most 16) and update row chunks: aim at a few
     // workgroups per CU.  The V update of a p-step is done by the next
     // p-step's inner launch, in about two workgroups per CU that the pivot
-    // pairs leave free (a workgroup there has 16 * 2w threads).
+    // pairs leave free (a workgroup there has 16 * 2w threads; at 2w = 64 its
+    // 138 KiB of LDS leave room for one at a time).
     const int target_wg = shp.update_wg;
     int64_t rps = 0;
     const int splits = gram_splits(m, npairs, split_target(h, o, shp, m, npairs, bw, fused), &rps);
@@ -1729,7 +1731,7 @@ BatchRoute batch_route(const jsvd_handle_s *h, int64_t batch, int32_t max_m, int
 }
 
 // Enqueue the batched solve with its workspace at ws (batch_plan(h,
-// batch).total bytes): the work-order kernels, then the two persistent
+// batch).total bytes): the work-order kernels, then the persistent
 // launches.  Allocates nothing.
 int launch_batched_solve(jsvd_handle_s *h, int64_t batch, int32_t max_m, int32_t max_n,
                          const int32_t *m,

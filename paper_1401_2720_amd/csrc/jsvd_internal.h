@@ -54,7 +54,7 @@ enum Counter {
     C_ROT = 0,       // inner rotations
     C_PROPER = 1,    // inner rotations with cs != 1
     C_CLAMP = 2,     // |coth 2phi| substitutions
-    C_BREAKDOWN = 3, // non-positive Cholesky pivots
+    C_BREAKDOWN = 3, // non-positive diagonal entries of H, or Cholesky pivots
     C_INNER_SW = 4,  // inner sweeps
     C_UPDATES = 5,   // pivot block-pairs with a transformation to apply
     C_NONFINITE = 6, // NaN met in a pivot Gram matrix
@@ -145,7 +145,8 @@ hipError_t launch_update(int bw, const StepArgs &a, hipStream_t s);
 // values, U and the output order.  counters (C_COUNT, any memory the device can
 // write) are set, C_SOLVE included.
 hipError_t launch_solve(const StepArgs &a, hipStream_t s);
-// Its largest number of rows: one CU streams 768 x 32 in about 265 us for the solve
+// Its largest number of rows (reached by the hyperbolic SVD and with qr off; else m >=
+// 2n goes through QR): one CU streams 768 x 32 in about 265 us for the solve
 // (launches per sweep: 306 us; 24 x 17: 131 against 255; 1024 x 32: 315 against 306).
 constexpr int64_t kSolveMaxM = 768;
 hipError_t launch_fused(int nquads, const StepArgs &a, hipStream_t s);

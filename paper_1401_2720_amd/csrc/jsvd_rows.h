@@ -99,8 +99,8 @@ __device__ __forceinline__ void update_rows(double *X, int64_t ldx, int64_t r0, 
 // doubles) laid out as in update_rows; the columns of the first two, and rows
 // and columns of the last two, are taken round by w where it takes that to
 // bring a0 (b0; a0, a1) first.  A pair that did not rotate takes part with the
-// identity.  Bound by the MFMAs: 256 per wave and slice against 32 KiB of
-// traffic, that is 16384 cycles for the four slices of a SIMD's waves.
+// identity.  Bound by the MFMAs: 256 per wave and slice (64 cycles each: 16384, or 7
+// us, for every slice that a SIMD takes) against 32 KiB of traffic.
 template <int NW>
 __device__ __forceinline__ void update_quad_rows(double *X, int64_t ldx, int64_t r0, int64_t r1,
                                                  const int *qd, const StepArgs &a, double *vs,
