@@ -168,3 +168,44 @@ def test_the_sort_leaves_short_problems_to_waves():
     assert np.array_equal(b.results(0)[0].ravel(order="F"), by_wave)
     ref = oracle.gesvj(big)["S"]
     assert np.all(np.abs(b.results(1)[1] - ref) <= 1e-12 * ref + 1e-13 * ref[0])
+
+
+def test_the_sort_decides_anew_at_every_replay():
+    """The sizes of a captured batch may change between replays (within its bounds):
+    the sort gives the problems to waves or to workgroups each time, and the bits are
+    those of an eager call."""
+    torch, jsvd = _jsvd()
+    from paper_1401_2720_amd import _binding as B
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    count, m, n = 2 * cus + 40, 100, 24
+    g = np.random.default_rng(3)
+    b = jsvd.Batch([g.standard_normal((m, n)) for _ in range(count)])
+    assert B.batched_kernels(b) == {"wave", "pointwise"}
+    small = torch.full_like(b.n, 5)
+    small[0] = n
+    sizes = {"all": torch.full_like(b.n, n), "one": small}
+    eager = {}
+    for name, ns in sizes.items():
+        b.n.copy_(ns)
+        jsvd.gesvd_batched(b)
+        torch.cuda.synchronize()
+        eager[name] = [x.clone() for x in (b.A, b.S, b.V)]
+    graph, side = torch.cuda.CUDAGraph(), torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        with torch.cuda.graph(graph, stream=side):
+            jsvd.gesvd_batched(b, restore=False)
+    torch.cuda.current_stream().wait_stream(side)
+    for name in ("one", "all", "one", "all", "all"):
+        b.n.copy_(sizes[name])
+        b.A.copy_(b.A0)
+        b.S.copy_(eager[name][1]).mul_(0.0 if name == "all" else 1.0)
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        used = [slice(None)] * 3
+        if name == "one":  # the others' buffers beyond 5 columns keep what was there
+            used = [slice(0, m * n), slice(0, n), slice(0, n * n)]
+        for x, y, u in zip((b.A, b.S, b.V), eager[name], used):
+            assert torch.equal(x[u], y[u]), name
+        assert int(b.status.abs().sum()) == 0
