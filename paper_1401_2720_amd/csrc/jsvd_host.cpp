@@ -1716,12 +1716,14 @@ BatchRoute batch_route(const jsvd_handle_s *h, int64_t batch, int32_t max_m, int
     // workgroups take turns.  How often they do depends on all sizes, not only on
     // the bounds, so from `few` problems to kWaveManyTurns times as many both
     // kernels are launched (an empty launch: 6 us) and the sort decides
-    // (batch_scan_kernel).
+    // (batch_scan_kernel); from the first problem on where the bound on m may be
+    // that of larger problems (n 8..80, m up to 90, no V: 300 1324 and 1395 us
+    // without waves).
     const int64_t cus = h->cu_count;
     const bool long_cols = max_m > wave_rows(max_n);
     const int64_t few = long_cols ? (max_n <= 8 ? cus : 2 * cus)
-                        : max_n > 16 && o.want_v && max_m + max_n > kWaveRowsV ? cus : 0;
-    const bool fits = want <= kWaveMaxLds && batch > few;
+                        : max_n > 16 && o.want_v && max_m + wn > kWaveRowsV ? cus : 0;
+    const bool fits = want <= kWaveMaxLds && (batch > few || (long_cols && max_n > kWaveMaxN));
     r.wave_lds = !r.ddrjac && (fits || batch >= kWaveMinBatch)
                      ? (int)std::min<int64_t>(want, kWaveMaxLds) : 0;
     r.wave_few = r.wave_lds && fits && long_cols && batch <= kWaveManyTurns * few ? (int)few : 0;
